@@ -117,13 +117,19 @@ struct Plan {
     std::map<int, std::unique_ptr<DevBuf>> dec_tasks;
     std::map<int, int> ndec;
     // bin tiles, rebuilt when strides change
-    DevBuf bin_tiles;
+    struct Tiles {
+        DevBuf tiles;
+        int n = 0;
+        int rev = 0;                      // revisits per tile part
+    };
+    Tiles resid, chisq;                   // the residual's parts, the chi^2's
     int nbin = 0;
     std::vector<int> bin_stride;          // per band, as used for bin_tiles
     // binning runs: tiles over chains of one detector pair's segments across
     // consecutive scans, and the (segment, phase offset) list they index
     DevBuf run_tiles, run_segs;
     int nrun_tiles = 0;
+    int run_rev = 0;
     int run_want = -1;                    // tod_set_bin_runs value the runs were built for
     std::vector<int> run_stride;          // strides the runs were built for
 };
@@ -286,6 +292,10 @@ std::vector<T> xcd_order(const std::vector<T> &v, Key key, const T &empty) {
     }
     size_t len = 0;
     for (const auto &l : lists) len = std::max(len, l.size());
+    // few or uneven groups would leave XCDs idle (one scan's four segments
+    // occupy four of the eight): then the items go round-robin as they come.
+    // Such sets fit the last-level cache that the XCDs share.
+    if (5 * len * kXcd > 8 * v.size()) return v;
     std::vector<T> out;
     out.reserve(len * kXcd);
     for (size_t j = 0; j < len; ++j)
@@ -310,7 +320,37 @@ RowTask empty_row() {
 }
 std::vector<int4> xcd_order_tiles(const std::vector<int4> &v) {
     if (v.empty()) return v;
-    return xcd_order(v, [](const int4 &t) { return t.x; }, make_int4(v[0].x, 0, 1, 0));
+    return xcd_order(v, [](const int4 &t) { return t.x; }, make_tile(v[0].x, 0, 1, 0, 0, 0));
+}
+
+// A strided tile and the most revisits its lanes make in one segment.
+struct TileWork {
+    int4 tile;
+    int visits;
+};
+// Tiles cut along time into parts of rev revisits (a multiple of the kernels'
+// eight in flight), rev as large as leaves about `want` parts: a set of few
+// scans has too few tiles to fill the chip, and a lane's serial walk through
+// its segment would bound the pass.  Parts of one tile touch the same pixels,
+// so more parts than that only add flushes.
+std::vector<int4> split_tiles(const std::vector<TileWork> &v, int64_t want, int &rev) {
+    int64_t sum = 0;
+    int most = 0;
+    for (const TileWork &t : v) {
+        sum += t.visits;
+        most = std::max(most, t.visits);
+    }
+    int64_t r = std::max<int64_t>(sum / std::max<int64_t>(want, 1), most / C3_TILE_MAXPART + 1);
+    r = std::max<int64_t>(8, (r + 7) / 8 * 8);
+    rev = (int)std::min<int64_t>(r, INT32_MAX);
+    std::vector<int4> out;
+    for (const TileWork &t : v)
+        for (int q = 0; (int64_t)q * rev < t.visits; ++q) {
+            int4 x = t.tile;
+            x.w |= q << 15;
+            out.push_back(x);
+        }
+    return out;
 }
 
 tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key, Plan **out) {
@@ -641,8 +681,15 @@ tod_status probe_stride(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t
     return TOD_OK;
 }
 
-tod_status get_bin_tiles(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t *pix,
-                         const int4 **tiles, int *ntile) {
+// Parts a launch of strided tiles is cut into.  The residual only writes its
+// samples: the more parts the shorter a lane's serial walk (5.5e6 samples of a
+// 30 GHz-like set: 40 us with 512 parts, 34 with 1024, 28 with 2048).  A part of
+// the binning or the map adjoint also writes its pixels' sums once more
+// (binning the same set: 50 us with 512, 58 with 1024, 68 with 4096; the
+// chi^2 and its adjoint over 9.2e6 samples: 140, 131, 147 us with 512, 1024, 2048).
+constexpr int64_t kResidParts = 2048, kBinParts = 512, kChisqParts = 1024;
+
+tod_status get_bin_tiles(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t *pix) {
     std::vector<int> st(L->nband, 0);
     for (int b = 0; b < L->nband; ++b) {
         auto it = ctx->band_stride.find(b);
@@ -663,9 +710,8 @@ tod_status get_bin_tiles(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_
     }
     if (st != P->bin_stride || P->nbin == 0) {
         // tiles over groups of up to two consecutive segments of equal length
-        // and band (one horn's radiometers share pointing); phases in the low
-        // 16 bits of .w, the group size above them
-        std::vector<int4> v;
+        // and band (one horn's radiometers share pointing)
+        std::vector<TileWork> tw;
         std::vector<char> done(L->nseg, 0);
         for (int s : P->seg_order) {
             if (done[s]) continue;
@@ -683,16 +729,17 @@ tod_status get_bin_tiles(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_
             const int S = std::max(1, std::min(st[P->h_segs[first].band], std::max(n, 1)));
             const int nph = std::min(S, n);
             for (int p0 = 0; p0 < nph; p0 += C3_NT)
-                v.push_back(make_int4(first, p0, S, std::min(C3_NT, nph - p0) | (grp << 16)));
+                tw.push_back({make_tile(first, p0, S, std::min(C3_NT, nph - p0), grp, 0), (n + S - 1) / S});
         }
-        v = xcd_order_tiles(v);
-        HIPCHK(P->bin_tiles.upload(v, ctx->stream));
-        P->nbin = (int)v.size();
+        for (Plan::Tiles *d : {&P->resid, &P->chisq}) {
+            const std::vector<int4> v = xcd_order_tiles(split_tiles(tw, d == &P->resid ? kResidParts : kChisqParts, d->rev));
+            HIPCHK(d->tiles.upload(v, ctx->stream));
+            d->n = (int)v.size();
+        }
+        P->nbin = P->resid.n;
         P->bin_stride = st;
         P->gen = ++ctx->gen_counter;  // graphs captured with the old tiles no longer match
     }
-    *tiles = (const int4 *)P->bin_tiles.p;
-    *ntile = P->nbin;
     return TOD_OK;
 }
 
@@ -710,11 +757,9 @@ tod_status get_bin_tiles(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_
 // phases [0, min(S, n)), as before.
 tod_status get_bin_runs(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t *pix,
                         const int4 **tiles, int *ntile, const int2 **runs) {
-    const int4 *pt;
-    int np;
-    tod_status r = get_bin_tiles(ctx, L, P, pix, &pt, &np);
+    tod_status r = get_bin_tiles(ctx, L, P, pix);
     if (r != TOD_OK) return r;
-    if (P->run_want != ctx->bin_runs || P->run_stride != P->bin_stride || (P->nrun_tiles == 0 && np > 0)) {
+    if (P->run_want != ctx->bin_runs || P->run_stride != P->bin_stride || (P->nrun_tiles == 0 && P->nbin > 0)) {
         const int nseg = L->nseg;
         const std::vector<int> &st = P->bin_stride;
         auto n_of = [&](int s) { return P->h_segs[s].n; };
@@ -750,7 +795,9 @@ tod_status get_bin_runs(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t
         } else if (G <= 0) {
             int64_t t1 = 0;
             for (const Pr &q : pairs) t1 += (std::min(S_of(q.first), std::max(n_of(q.first), 0)) + C3_NT - 1) / C3_NT;
-            G = (int)std::max<int64_t>(1, std::min<int64_t>(16, t1 / 4096));
+            // 9.4e8 samples, t1 = 34200: 3.27 ms with runs of one scan, 3.17 with two,
+            // 3.24 with four, 3.43 with eight
+            G = (int)std::max<int64_t>(1, std::min<int64_t>(16, t1 / 16384));
         }
         // chains of pairs of one detector pair (long pairs only), in index order
         std::map<std::tuple<int, int, int>, std::vector<int>> chains;
@@ -778,7 +825,7 @@ tod_status get_bin_runs(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t
                              return run_samples(a) > run_samples(b);
                          });
         std::vector<int2> segs;
-        std::vector<int4> tl;
+        std::vector<TileWork> tw;
         for (const std::vector<int> &rp : runs_of_pairs) {
             const int first = (int)segs.size();
             const int s0 = pairs[rp[0]].first;
@@ -791,10 +838,12 @@ tod_status get_bin_runs(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t
                     segs.push_back(make_int2(sg, multi ? (int)(A[sg] % S) : 0));
                 }
             const int nsg = (int)segs.size() - first;
+            int visits = 0;
+            for (int i : rp) visits = std::max(visits, (n_of(pairs[i].first) + S - 1) / S);
             for (int p0 = 0; p0 < nph; p0 += C3_NT)
-                tl.push_back(make_int4(first, p0, S, std::min(C3_NT, nph - p0) | (nsg << 16)));
+                tw.push_back({make_tile(first, p0, S, std::min(C3_NT, nph - p0), nsg, 0), visits});
         }
-        tl = xcd_order_tiles(tl);
+        const std::vector<int4> tl = xcd_order_tiles(split_tiles(tw, kBinParts, P->run_rev));
         HIPCHK(P->run_tiles.upload(tl, ctx->stream));
         HIPCHK(P->run_segs.upload(segs, ctx->stream));
         P->nrun_tiles = (int)tl.size();
@@ -807,6 +856,13 @@ tod_status get_bin_runs(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t
     *runs = (const int2 *)P->run_segs.p;
     return TOD_OK;
 }
+
+// The strided kernels read T, Q, U once per pixel change: three cache lines
+// from the [3][npix] maps, or one from records interleaved first, which costs
+// a pass over the whole map.  Interleaving all 12.6e6 pixels of nside 1024 takes
+// 55 us: with 1e8 samples over them the residual took 418 us with records and
+// 385 without; with 9.4e8 samples 3.00 ms with and 3.28 without.
+bool map_records(const tod_layout *L) { return L->nsamp >= 16 * L->npix_total; }
 
 c3::FftArgs fft_args(tod_ctx ctx, Plan *P, const tod_layout *L) {
     c3::FftArgs a;
@@ -1106,13 +1162,12 @@ tod_status project_sky(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const 
     Plan *P;
     if ((r = get_plan(ctx, lay, mixed, &P)) != TOD_OK) return r;
     // strided tiles (the revisit period is probed from pix on first use)
-    const int4 *tiles;
-    int nt;
-    if ((r = get_bin_tiles(ctx, lay, P, pix, &tiles, &nt)) != TOD_OK) return r;
-    HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
+    if ((r = get_bin_tiles(ctx, lay, P, pix)) != TOD_OK) return r;
+    const bool rec = map_records(lay);
+    if (rec) HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
     KTimer kt(ctx, K_PROJECT, ctx->stream);
-    HIPCHK(c3::launch_resid_tiles(ctx->stream, make_layout_dev(lay), mixed, tiles, nt, pix, psi, nullptr, 0,
-                                  maps, ctx->maps4.p, gain, mixed ? ctx->trig32.p : ctx->trig64.p, s_out,
+    HIPCHK(c3::launch_resid_tiles(ctx->stream, make_layout_dev(lay), mixed, (const int4 *)P->resid.tiles.p, P->resid.n,
+                                  P->resid.rev, pix, psi, nullptr, 0, maps, rec ? ctx->maps4.p : nullptr, gain, mixed ? ctx->trig32.p : ctx->trig64.p, s_out,
                                   nullptr));
     return TOD_OK;
 }
@@ -1487,7 +1542,7 @@ tod_status bin_tod(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const int3
     HIPCHK(c3::launch_check_params(ctx->stream, Ld, sigma0, nullptr, nullptr, ctx->d_err));
     if (!accumulate) HIPCHK(c3::launch_zero(ctx->stream, acc, lay->npix_total * 10 * sizeof(double)));
     KTimer kt(ctx, K_BIN, ctx->stream);
-    HIPCHK(c3::launch_bin_tiles(ctx->stream, Ld, mixed, tiles, nt, runs, pix, psi, d, d_dtype == TOD_F64, ncorr,
+    HIPCHK(c3::launch_bin_tiles(ctx->stream, Ld, mixed, tiles, nt, P->run_rev, runs, pix, psi, d, d_dtype == TOD_F64, ncorr,
                                 gain, sigma0, ctx->trig64.p, acc, ctx->d_err));
     return TOD_OK;
 }
@@ -1518,32 +1573,33 @@ static tod_status chisq_common(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     Plan *P;
     if ((r = get_plan(ctx, lay, mixed, &P)) != TOD_OK) return r;
     if ((r = ensure_work(ctx, P)) != TOD_OK) return r;
-    const int4 *tiles;
-    int nt;
-    if ((r = get_bin_tiles(ctx, lay, P, pix, &tiles, &nt)) != TOD_OK) return r;
+    if ((r = get_bin_tiles(ctx, lay, P, pix)) != TOD_OK) return r;
     const size_t ssz = sizeof(double) * 4 * (size_t)std::max(1, lay->nseg);
     HIPCHK(ctx->seg_sums.ensure(ssz));
     HIPCHK(ctx->seg_whittle.ensure(ssz));
     hipStream_t st = ctx->stream;
     HIPCHK(c3::launch_zero(st, ctx->seg_sums.p, ssz));
     HIPCHK(c3::launch_zero(st, ctx->seg_whittle.p, ssz));
-    if (grad_maps) {
+    // the map gradient gathers in records of four where the maps are read so
+    double *gm = grad_maps;
+    if (grad_maps && map_records(lay)) {
         HIPCHK(ctx->gmap4.ensure(sizeof(double) * 4 * (size_t)std::max<int64_t>(1, lay->npix_total)));
-        HIPCHK(c3::launch_zero(st, ctx->gmap4.p, sizeof(double) * 4 * lay->npix_total));
+        gm = (double *)ctx->gmap4.p;
     }
+    if (gm) HIPCHK(c3::launch_zero(st, gm, (int64_t)sizeof(double) * (gm == grad_maps ? 3 : 4) * lay->npix_total));
     if (gsig) HIPCHK(c3::launch_zero(st, gsig, sizeof(double) * lay->ndet));
     if (gfk) HIPCHK(c3::launch_zero(st, gfk, sizeof(double) * lay->ndet));
     if (galpha) HIPCHK(c3::launch_zero(st, galpha, sizeof(double) * lay->ndet));
-    HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
+    const bool rec = map_records(lay);
+    if (rec) HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
     const LayoutDev Ld = make_layout_dev(lay);
     HIPCHK(c3::launch_check_params(st, Ld, sigma0, fknee, alpha, ctx->d_err));
     {
         KTimer kt(ctx, K_CHISQ, st);
-        double *g4 = grad_maps ? (double *)ctx->gmap4.p : nullptr;
-        HIPCHK(c3::launch_chisq_time_tiles(st, Ld, mixed, tiles, nt, pix, psi, d, d_dtype == TOD_F64,
-                                           ncorr, maps, ctx->maps4.p, gain, sigma0, ctx->trig64.p,
-                                           (double *)ctx->seg_sums.p, g4, gscale, gscale_dev));
-        if (grad_maps) HIPCHK(c3::launch_gmap_out(st, lay->npix_total, g4, grad_maps));
+        HIPCHK(c3::launch_chisq_time_tiles(st, Ld, mixed, (const int4 *)P->chisq.tiles.p, P->chisq.n, P->chisq.rev,
+                                           pix, psi, d, d_dtype == TOD_F64, ncorr, maps, rec ? ctx->maps4.p : nullptr, gain, sigma0, ctx->trig64.p,
+                                           (double *)ctx->seg_sums.p, gm, gscale, gscale_dev));
+        if (gm != grad_maps) HIPCHK(c3::launch_gmap_out(st, lay->npix_total, gm, grad_maps));
     }
     c3::FftArgs a = fft_args(ctx, P, lay);
     a.in_a = ncorr;
@@ -1628,7 +1684,8 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
         if ((r = get_decode_tasks(ctx, P, tod->chunk_len, &dtt, &ndtt)) != TOD_OK) return r;
         HIPCHK(ctx->dec_tabs2.ensure(sizeof(DecTab) * (size_t)tod->ntable));
     }
-    HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
+    const bool rec = map_records(lay);
+    if (rec) HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
     hipStream_t st = ctx->stream;
     const LayoutDev Ld = make_layout_dev(lay);
     if (P->nbin > 0) {
@@ -1657,7 +1714,7 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
     gk = fnv(gk, &quantum, sizeof(quantum));
     const void *ptrs[] = {d, maps, gain, sigma0, fknee, alpha, ncorr_out, acc, pix_work, psi_work,
                           ctx->work.p, ctx->resid.p, ctx->dec_tabs.p, ctx->maps4.p, ctx->trig32.p,
-                          ctx->trig64.p, ctx->d_err, ctx->d_seed_iter, dt, P->bin_tiles.p, P->run_tiles.p,
+                          ctx->trig64.p, ctx->d_err, ctx->d_seed_iter, dt, P->resid.tiles.p, P->run_tiles.p,
                           P->run_segs.p, ctx->dec_tabs2.p, dtt};
     gk = fnv(gk, ptrs, sizeof(ptrs));
     gk = fnv(gk, &ndt, sizeof(ndt));
@@ -1689,21 +1746,17 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
             HIPCHK(c3::launch_decode_stream(st, Ld, Ht, (DecTab *)ctx->dec_tabs2.p, dtt, ndtt, mixed ? 0 : 1,
                                             quantum, 0, d_work, nullptr, ctx->d_err));
         }
-        const int4 *tiles = (const int4 *)P->bin_tiles.p;
-        int nt = P->nbin;
         const int4 *rtiles = (const int4 *)P->run_tiles.p;
         const int2 *runs = (const int2 *)P->run_segs.p;
         int nrt = P->nrun_tiles;
         if (!capture && !have_tiles) {
             tod_status rr = get_bin_runs(ctx, lay, P, pix_work, &rtiles, &nrt, &runs);
             if (rr != TOD_OK) return rr;
-            tiles = (const int4 *)P->bin_tiles.p;
-            nt = P->nbin;
         }
         {
             KTimer kt(ctx, K_PROJECT, st);
-            HIPCHK(c3::launch_resid_tiles(st, Ld, mixed, tiles, nt, pix_work, psi_work, d,
-                                          d_dtype == TOD_F64, maps, ctx->maps4.p, gain,
+            HIPCHK(c3::launch_resid_tiles(st, Ld, mixed, (const int4 *)P->resid.tiles.p, P->resid.n,
+                                          P->resid.rev, pix_work, psi_work, d, d_dtype == TOD_F64, maps, rec ? ctx->maps4.p : nullptr, gain,
                                           mixed ? ctx->trig32.p : ctx->trig64.p, ctx->resid.p, ctx->d_err));
         }
         {
@@ -1722,7 +1775,7 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
         {
             HIPCHK(c3::launch_zero(st, acc, lay->npix_total * 10 * sizeof(double)));
             KTimer kt(ctx, K_BIN, st);
-            HIPCHK(c3::launch_bin_tiles(st, Ld, mixed, rtiles, nrt, runs, pix_work, psi_work, d,
+            HIPCHK(c3::launch_bin_tiles(st, Ld, mixed, rtiles, nrt, P->run_rev, runs, pix_work, psi_work, d,
                                         d_dtype == TOD_F64, ncorr_out, gain, sigma0, ctx->trig64.p, acc,
                                         ctx->d_err));
         }

@@ -160,6 +160,15 @@ struct alignas(16) DecTab {
     int32_t pad[2];
 };
 
+// Strided tile of the pixel-domain kernels: x = first segment (or run entry),
+// y = first phase, z = stride S, w = lanes | group size << 9 | part << 15.
+// Part q covers the revisits [q rev, (q + 1) rev) of each segment.
+#define C3_TILE_MAXGRP 32
+#define C3_TILE_MAXPART 65535
+inline int4 make_tile(int first, int phi0, int S, int nph, int ngrp, int part) {
+    return make_int4(first, phi0, S, nph | (ngrp << 9) | (part << 15));
+}
+
 // Decode work item: one block decodes up to C3_NT consecutive chunks of one segment.
 struct DecodeTask {
     int32_t seg;
@@ -201,13 +210,14 @@ hipError_t launch_decode_stream(hipStream_t st, const LayoutDev &L, const HuffDe
                                 uint32_t flag_mask, void *out, uint8_t *mask_out, uint32_t *err);
 
 // r = d - g P m on strided tiles (the sweep's residual, input of the n_corr FFTs),
-// or s = g P m when d is NULL; maps4: workspace of npix_total records of 4
-// values (T, Q, U, 0), filled from the [3][npix] maps first
+// or s = g P m when d is NULL; rev: revisits per tile part; maps4: workspace of
+// npix_total records of 4 values (T, Q, U, 0), filled from the [3][npix] maps
+// first, or NULL to read the maps themselves
 // trig: the cos/sin 2psi table of the precision's type; err: sticky word that
 // receives C3_ERR_NONFINITE where d - s is not finite at an in-range pixel
 // (may be NULL)
 hipError_t launch_resid_tiles(hipStream_t st, const LayoutDev &L, int mixed, const int4 *tiles,
-                              int ntile, const int32_t *pix, const uint16_t *psi, const void *d,
+                              int ntile, int rev, const int32_t *pix, const uint16_t *psi, const void *d,
                               int d_f64, const void *maps, void *maps4, const double *gain,
                               const void *trig, void *r_out, uint32_t *err);
 // per non-empty segment: sigma0 > 0, f_knee > 0, alpha < 0, all finite (any
@@ -269,7 +279,7 @@ hipError_t fft_init_attributes();
 
 // tiles and runs: the binning runs (get_bin_runs); err receives C3_ERR_NONFINITE
 hipError_t launch_bin_tiles(hipStream_t st, const LayoutDev &L, int mixed, const int4 *tiles,
-                            int ntile, const int2 *runs, const int32_t *pix, const uint16_t *psi,
+                            int ntile, int rev, const int2 *runs, const int32_t *pix, const uint16_t *psi,
                             const void *d, int d_f64, const void *ncorr, const double *gain,
                             const double *sigma0, const void *trig64, double *acc, uint32_t *err);
 hipError_t launch_zero(hipStream_t st, void *p, int64_t bytes);
@@ -279,15 +289,15 @@ hipError_t launch_repeat_probe(hipStream_t st, const int32_t *pix, int64_t off, 
                                unsigned long long *counts);
 
 // chi^2 time-domain part on strided tiles: per segment sum r^2/sigma0^2 (-> seg_sums[4s]),
-// sum (Pm) r (-> [4s+1]), sum r^2 (-> [4s+2]); with grad_maps4 != NULL also the map adjoint,
-// added to grad_maps4: npix_total records (T, Q, U, unused) of FP64, zeroed by the caller.
-// maps4: workspace of npix_total records (T, Q, U, 0), filled from the [3][npix] maps first.
+// sum (Pm) r (-> [4s+1]), sum r^2 (-> [4s+2]); with gmap != NULL also the map adjoint, added to
+// gmap (FP64, zeroed by the caller): npix_total records (T, Q, U, unused) with maps4, else the
+// [3][npix_total] planes.  maps4 as in launch_resid_tiles.
 hipError_t launch_chisq_time_tiles(hipStream_t st, const LayoutDev &L, int mixed, const int4 *tiles,
-                                   int ntile, const int32_t *pix, const uint16_t *psi,
+                                   int ntile, int rev, const int32_t *pix, const uint16_t *psi,
                                    const void *d, int d_f64, const void *ncorr, const void *maps,
                                    void *maps4, const double *gain, const double *sigma0,
-                                   const void *trig64, double *seg_sums, double *grad_maps4,
-                                   double grad_scale, const double *gscale_dev);
+                                   const void *trig64, double *seg_sums, double *gmap, double grad_scale,
+                                   const double *gscale_dev);
 // grad_maps [3][npt] from the records of grad_maps4
 hipError_t launch_gmap_out(hipStream_t st, int64_t npt, const double *grad_maps4, double *grad_maps);
 hipError_t launch_chisq_finish(hipStream_t st, const LayoutDev &L, const double *seg_time,

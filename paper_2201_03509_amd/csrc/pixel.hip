@@ -10,22 +10,151 @@
 // registers and touches global memory (FP64 atomics) only when the pixel
 // changes.  Any S is correct; only the atomic traffic depends on it.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 
 namespace {
 
-// ---------------------------------------------------------------- binning
-// acc is pixel-major, [npt][10]: a flush adds to the ten words of one
-// pixel's record (one or two cache lines), not to ten lines npt apart.
-__device__ __forceinline__ void flush_acc(double *acc, int64_t npt, int64_t gp, const double *a) {
-    (void)npt;
-#pragma unroll
-    for (int j = 0; j < 10; ++j) atomicAdd(acc + gp * 10 + j, a[j]);
+// cos/sin 2psi of a psi bin from an LDS table staged by every block: they
+// repeat every 2048 bins.  FP64: a bin 512 later is a quarter turn further, so
+// the 512 entries of the first quadrant and two sign flips serve all bins
+// (8 KB instead of 32).  FP32: the 2048 entries themselves (16 KB).
+template <typename T>
+constexpr int kTrig = sizeof(T) == 8 ? 512 : 2048;
+template <typename T>
+__device__ __forceinline__ void trig_stage(cx<T> *tr, const cx<T> *__restrict__ trig) {
+    for (int b = threadIdx.x; b < kTrig<T>; b += C3_NT) tr[b] = trig[b];
+}
+template <typename T>
+__device__ __forceinline__ cx<T> trig_at(const cx<T> *tr, int b) {
+    constexpr int kN = kTrig<T>;
+    if constexpr (kN == 2048) return tr[b & 2047];
+    const cx<T> e = tr[b & (kN - 1)];
+    const bool odd = b & kN;                     // odd quadrant: (c, s) -> (-s, c)
+    const T x = odd ? e.y : e.x, y = odd ? e.x : e.y;
+    return cx<T>{((b ^ (b << 1)) & (2 * kN)) ? -x : x, (b & (2 * kN)) ? -y : y};
 }
 
-// Bin tile (x = first entry of the run list, y = first phase, z = stride S,
-// w = phases | entries << 16); run entry = (segment, phase offset o).  Lane
+// element t of a segment's array: scalar base, 32-bit byte offset
+template <typename V>
+__device__ __forceinline__ V at(const V *base, uint32_t t) {
+    return *(const V *)((const char *)base + t * (uint32_t)sizeof(V));
+}
+
+// Strided tile (common.h): first entry, first phase, stride S, and packed
+// lanes, group size and part.  Part q of a tile covers the revisits
+// [q rev, (q + 1) rev) of every segment of its group: sets with few tiles are
+// cut along time to fill the chip.
+struct Tile {
+    int first, phi0, S, nph, ngrp, part;
+};
+__device__ __forceinline__ Tile tile_of(int4 t) {
+    return Tile{t.x, t.y, t.z, t.w & 0x1FF, (t.w >> 9) & 0x3F, t.w >> 15};
+}
+// first visit of the part relative to its first sample, and the revisits it
+// covers in a segment of n samples (the same for every lane; a lane's own
+// visits end at n)
+__device__ __forceinline__ int part_visits(const Tile &tl, int n, int rev, int &t0) {
+    const int nv = (n + tl.S - 1) / tl.S;
+    const int64_t u0 = (int64_t)tl.part * rev;
+    t0 = u0 < nv ? (int)u0 * tl.S : 0;
+    return u0 < nv ? (int)min((int64_t)rev, nv - u0) : 0;
+}
+
+// ------------------------------------------------- per-pixel records to memory
+// NV sums per pixel of the lanes in `mask` (a wave's lanes, all of them
+// running) added to memory: the records go through LDS, and the wave's atomics
+// then walk them word by word, so that the ten words of a record are
+// consecutive lanes of one atomic instruction (one or two cache lines) instead
+// of ten instructions of 64 scattered lines each.  Neighbouring records of the
+// same pixel (coarse maps) are summed first.  rec(pixel, j): address of word j.
+constexpr int kRec = 32;  // records staged at a time
+template <int NV>
+struct RecLds {
+    double v[kRec * NV];
+    int p[kRec];
+};
+template <int NV, typename Rec>
+__device__ __forceinline__ void wave_flush(RecLds<NV> &L, unsigned long long mask, int pixel, const double *v,
+                                           Rec &&rec) {
+    const int lane = threadIdx.x & 63;
+    const int slot = __builtin_popcountll(mask & ((1ull << lane) - 1));
+    const int n = __builtin_popcountll(mask);
+    const bool mine = (mask >> lane) & 1;
+    for (int base = 0; base < n; base += kRec) {
+        const int m = min(kRec, n - base);
+        const int s = slot - base;
+        if (mine && s >= 0 && s < kRec) {
+            L.p[s] = pixel;
+#pragma unroll
+            for (int j = 0; j < NV; ++j) L.v[s * NV + j] = v[j];
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        for (int i = lane; i < m * NV; i += 64) {
+            const int r = i / NV, j = i - r * NV;
+            const int p = L.p[r];
+            if (r > 0 && L.p[r - 1] == p) continue;  // summed into the run's first record
+            double x = L.v[i];
+            for (int q = r + 1; q < m && L.p[q] == p; ++q) x += L.v[q * NV + j];
+            atomicAdd(rec(p, j), x);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// A lane's sums of the current pixel and the two before it (most recent
+// first), so a phase that crosses pixel edges or alternates between pixels
+// rarely writes before its tile ends: loads and atomics share one in-order
+// completion counter, so a revisit's loads also wait for the atomics before
+// them.  move() makes p current for the lanes with ev set; every lane of the
+// wave calls it together.
+template <int NV>
+struct Sums3 {
+    double a[NV], o[NV], q[NV];
+    int cur = -1, old = -1, older = -1;
+    __device__ __forceinline__ void clear() {
+#pragma unroll
+        for (int j = 0; j < NV; ++j) a[j] = o[j] = q[j] = 0.0;
+    }
+    template <typename Rec>
+    __device__ __forceinline__ void move(RecLds<NV> &L, bool ev, int p, Rec &&rec) {
+        const bool fresh = ev && p != old && p != older;
+        const unsigned long long out = __ballot(fresh && older >= 0);
+        if (out) wave_flush<NV>(L, out, older, q, rec);
+        if (!ev) return;
+        if (p == old) {  // a <-> o
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                const double x = a[j];
+                a[j] = o[j];
+                o[j] = x;
+            }
+        } else {  // q -> a -> o -> q, q cleared first when p is a new pixel
+#pragma unroll
+            for (int j = 0; j < NV; ++j) {
+                const double x = fresh ? 0.0 : q[j];
+                q[j] = o[j];
+                o[j] = a[j];
+                a[j] = x;
+            }
+            older = old;
+        }
+        old = cur;
+        cur = p;
+    }
+    template <typename Rec>
+    __device__ __forceinline__ void finish(RecLds<NV> &L, Rec &&rec) {
+        wave_flush<NV>(L, __ballot(cur >= 0), cur, a, rec);
+        wave_flush<NV>(L, __ballot(old >= 0), old, o, rec);
+        wave_flush<NV>(L, __ballot(older >= 0), older, q, rec);
+    }
+};
+
+// ---------------------------------------------------------------- binning
+// Bin tiles over the run list: entry = (segment, phase offset o).  Lane
 // phase Phi visits t = (Phi - o) mod S, + S, ... of each of the run's
 // segments in turn, so segments that see the same pixels (the two radiometers
 // of a horn, and the same horn's consecutive scans at equal spin phase) share
@@ -33,8 +162,12 @@ __device__ __forceinline__ void flush_acc(double *acc, int64_t npt, int64_t gp, 
 // TD: type of d, TN: type of n_corr (NC = false: no n_corr).  Both are
 // compile-time, so a revisit's loads issue back to back with no branch
 // between them and are converted only once all of them are in flight.
+// Bound by the sample reads and the accumulators' atomics.  70 GHz-like sets:
+// 1e8 samples 833 -> 416 us, 9.4e8 samples 4.05 -> 3.17 ms with the flushes as
+// records through LDS (wave_flush) and the small trigonometric table; one scan
+// of 4.6e5 samples 47 -> 17 us with the tiles cut along time.
 template <typename TN, typename TD, bool NC>
-__global__ __launch_bounds__(C3_NT) void k_bin(LayoutDev Ld, const int4 *__restrict__ tiles,
+__global__ __launch_bounds__(C3_NT) void k_bin(LayoutDev Ld, const int4 *__restrict__ tiles, int rev,
                                                const int2 *__restrict__ runs,
                                                const int32_t *__restrict__ pix,
                                                const uint16_t *__restrict__ psi,
@@ -44,125 +177,85 @@ __global__ __launch_bounds__(C3_NT) void k_bin(LayoutDev Ld, const int4 *__restr
                                                const double *__restrict__ sigma0,
                                                const cx<double> *__restrict__ trig,
                                                double *__restrict__ acc, uint32_t *__restrict__ err) {
-    // cos/sin 2psi repeat every 2048 psi bins
-    __shared__ cx<double> tr[2048];
-    const int4 tl = tiles[blockIdx.x];
-    for (int b = threadIdx.x; b < 2048; b += C3_NT) tr[b] = trig[b];
+    __shared__ cx<double> tr[kTrig<double>];
+    __shared__ RecLds<10> recs[C3_NT / 64];
+    const Tile tl = tile_of(tiles[blockIdx.x]);
+    if (tl.nph == 0) return;  // an empty tile (launch padding)
+    trig_stage(tr, trig);
     __syncthreads();
-    const int S = tl.z;
-    const int nph = tl.w & 0xFFFF, ngrp = tl.w >> 16;
-    const int phi = tl.y + threadIdx.x;
-    if ((int)threadIdx.x >= nph) return;
-    const int seg0 = runs[tl.x].x;
+    RecLds<10> &L = recs[threadIdx.x >> 6];
+    const int S = tl.S;
+    const int phi = tl.phi0 + threadIdx.x;
+    const bool act = (int)threadIdx.x < tl.nph;
+    const int seg0 = runs[tl.first].x;
     const int64_t poff = Ld.band[Ld.seg_band[seg0]].pix_off;
     const uint32_t npix = (uint32_t)Ld.band[Ld.seg_band[seg0]].npix;
-    const int64_t npt = Ld.npix_total;
-    // three register accumulators, the current pixel and the two before it
-    // (most recent first), so a phase that crosses pixel edges or alternates
-    // between pixels rarely flushes before its tile ends.  A flush inside the
-    // loop is costly beyond its atomics: loads and atomics share one in-order
-    // completion counter, so the next revisit's loads also wait for them.  On
-    // the 70 GHz-like set no lane meets a fourth pixel within a tile.
-    double a[10], o[10], q[10];
-#pragma unroll
-    for (int j = 0; j < 10; ++j) a[j] = o[j] = q[j] = 0.0;
-    int cur = -1, old = -1, older = -1;
-    double w = 0, gw = 0;
+    // acc is pixel-major, [npix_total][10]
+    auto rec = [&](int p, int j) { return acc + (poff + p) * 10 + j; };
+    Sums3<10> s3;
+    s3.clear();
     bool bad = false;  // a binned d - n_corr is not finite
-    auto step = [&](int p, int b, double v) {
-        if ((uint32_t)p >= npix) return;  // out-of-range pixels are not binned
-        bad |= !isfinite(v);
-        if (p != cur) {
-            if (p == old) {  // a <-> o
-#pragma unroll
-                for (int j = 0; j < 10; ++j) {
-                    const double x = a[j];
-                    a[j] = o[j];
-                    o[j] = x;
-                }
-                old = cur;
-                cur = p;
-            } else if (p == older) {  // q -> a -> o -> q
-#pragma unroll
-                for (int j = 0; j < 10; ++j) {
-                    const double x = q[j];
-                    q[j] = o[j];
-                    o[j] = a[j];
-                    a[j] = x;
-                }
-                older = old;
-                old = cur;
-                cur = p;
-            } else {  // a new pixel: the least recent one leaves
-                if (older >= 0) flush_acc(acc, npt, poff + older, q);
-#pragma unroll
-                for (int j = 0; j < 10; ++j) {
-                    q[j] = o[j];
-                    o[j] = a[j];
-                    a[j] = 0.0;
-                }
-                older = old;
-                old = cur;
-                cur = p;
-            }
-        }
-        const cx<double> cs = tr[b & 2047];
-        const double wv = w * v;
-        a[0] += wv;
-        a[1] += wv * cs.x;
-        a[2] += wv * cs.y;
-        a[3] += gw;
-        a[4] += gw * cs.x;
-        a[5] += gw * cs.y;
-        a[6] += gw * cs.x * cs.x;
-        a[7] += gw * cs.x * cs.y;
-        a[8] += gw * cs.y * cs.y;
-        a[9] += 1.0;
-    };
-    for (int gi = 0; gi < ngrp; ++gi) {
-        const int2 re = runs[tl.x + gi];
+    for (int gi = 0; gi < tl.ngrp; ++gi) {
+        const int2 re = runs[tl.first + gi];
         const int seg = re.x;
         if (Ld.seg_accept && !Ld.seg_accept[seg]) continue;
         const int64_t s0 = Ld.seg_off[seg];
         const int n = (int)(Ld.seg_off[seg + 1] - s0);
         const double g = gain[seg];
-        const double s2 = sigma0[seg];
-        w = g / (s2 * s2);
-        gw = g * w;
+        const double sg = sigma0[seg];
+        const double w = g / (sg * sg), gw = g * w;
+        int t0;
+        const int cnt = part_visits(tl, n, rev, t0);
+        const int32_t *pixs = pix + s0;
+        const uint16_t *psis = psi + s0;
+        const TD *ds = d + s0;
+        const TN *ns = NC ? ncorr + s0 : nullptr;
         int t = phi - re.y;  // the offset is in [0, S): one wrap at most
         if (t < 0) t += S;
+        t += t0;
         // eight revisits in flight (with the flushes' atomics on one record
         // each, loads in flight bound the pass: 4.64 ms with two, 4.19 with
-        // four, 4.10 with eight on the 70 GHz-like set)
-        for (; t + 7 * S < n; t += 8 * S) {
+        // four, 4.10 with eight on the 70 GHz-like set); beyond the segment's
+        // end a lane repeats its last sample and leaves it out
+        for (int u0 = 0; u0 < cnt; u0 += 8, t += 8 * S) {
             int p[8], b[8];
             TD dv[8];
             TN nv[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int64_t i = s0 + t + u * S;
-                p[u] = pix[i];
-                b[u] = psi[i];
-                dv[u] = d[i];
-                if constexpr (NC) nv[u] = ncorr[i];
+                const uint32_t i = (uint32_t)min(t + u * S, n - 1);
+                p[u] = at(pixs, i);
+                b[u] = at(psis, i);
+                dv[u] = at(ds, i);
+                if constexpr (NC) nv[u] = at(ns, i);
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
                 double v = (double)dv[u];
                 if constexpr (NC) v -= (double)nv[u];
-                step(p[u], b[u], v);
+                // out-of-range pixels are not binned
+                const bool ok = act && t + u * S < n && (uint32_t)p[u] < npix;
+                const bool ev = ok && p[u] != s3.cur;
+                if (__ballot(ev)) s3.move(L, ev, p[u], rec);
+                if (ok) {
+                    bad |= !isfinite(v);
+                    const cx<double> cs = trig_at(tr, b[u]);
+                    const double wv = w * v, gx = gw * cs.x, gy = gw * cs.y;
+                    s3.a[0] += wv;
+                    s3.a[1] += wv * cs.x;
+                    s3.a[2] += wv * cs.y;
+                    s3.a[3] += gw;
+                    s3.a[4] += gx;
+                    s3.a[5] += gy;
+                    s3.a[6] += gx * cs.x;
+                    s3.a[7] += gx * cs.y;
+                    s3.a[8] += gy * cs.y;
+                    s3.a[9] += 1.0;
+                }
             }
         }
-        for (; t < n; t += S) {
-            const int64_t i = s0 + t;
-            double v = (double)d[i];
-            if constexpr (NC) v -= (double)ncorr[i];
-            step(pix[i], psi[i], v);
-        }
     }
-    if (cur >= 0) flush_acc(acc, npt, poff + cur, a);
-    if (old >= 0) flush_acc(acc, npt, poff + old, o);
-    if (older >= 0) flush_acc(acc, npt, poff + older, q);
+    s3.finish(L, rec);
     if (bad && err) atomicOr(err, C3_ERR_NONFINITE);
 }
 
@@ -171,11 +264,21 @@ __global__ __launch_bounds__(C3_NT) void k_bin(LayoutDev Ld, const int4 *__restr
 // tiles; the thread keeps the map values of its current pixel in registers
 // across revisits (and across the tile's segments), so the map is read once
 // per pixel change instead of once per sample.
-// T, Q, U of one pixel in one aligned record (one load per pixel change)
+
+// T, Q, U of one pixel in one aligned record (one cache line per pixel change)
 template <typename T>
 struct alignas(4 * sizeof(T)) Stokes4 {
     T t, q, u, pad;
 };
+
+// T, Q, U of pixel p from records (REC) or from the [3][npt] planes.  A
+// compile-time choice: a run-time branch around the loads cost the residual
+// 6 % (3.10 against 2.93 ms on the 9.4e8-sample 70 GHz-like set).
+template <bool REC, typename T>
+__device__ __forceinline__ Stokes4<T> map_at(const T *m, int64_t npt, int p) {
+    if constexpr (REC) return ((const Stokes4<T> *)m)[p];
+    return Stokes4<T>{m[p], m[npt + p], m[2 * npt + p], (T)0};
+}
 
 // [3][npix] maps -> [npix] records
 template <typename T>
@@ -193,68 +296,70 @@ __global__ __launch_bounds__(C3_NT) void k_interleave(const T *__restrict__ maps
 // result is already residual-sized (about 2e-6 of r against 2e-5 for r =
 // d - g (T + Q c + U s) in float).  FP64: the plain sum.  With SUB a lane
 // that meets a non-finite d - s at an in-range pixel raises C3_ERR_NONFINITE.
-template <typename T, typename TD, bool SUB>
-__global__ __launch_bounds__(C3_NT) void k_resid(LayoutDev Ld, const int4 *__restrict__ tiles,
+template <typename T, typename TD, bool SUB, bool REC>
+__global__ __launch_bounds__(C3_NT) void k_resid(LayoutDev Ld, const int4 *__restrict__ tiles, int rev,
                                                  const int32_t *__restrict__ pix,
                                                  const uint16_t *__restrict__ psi,
                                                  const TD *__restrict__ d,
-                                                 const Stokes4<T> *__restrict__ maps,
+                                                 const T *__restrict__ maps,
                                                  const double *__restrict__ gain,
                                                  const cx<T> *__restrict__ trig,
                                                  T *__restrict__ r_out, uint32_t *__restrict__ err) {
-    __shared__ cx<T> tr[2048];
-    const int4 tl = tiles[blockIdx.x];
-    for (int b = threadIdx.x; b < 2048; b += C3_NT) tr[b] = trig[b];
+    __shared__ cx<T> tr[kTrig<T>];
+    const Tile tl = tile_of(tiles[blockIdx.x]);
+    if (tl.nph == 0) return;  // an empty tile (launch padding)
+    trig_stage(tr, trig);
     __syncthreads();
-    const int S = tl.z;
-    const int nph = tl.w & 0xFFFF, ngrp = tl.w >> 16;
-    const int phi = tl.y + threadIdx.x;
-    if ((int)threadIdx.x >= nph) return;
-    const int band = Ld.seg_band[tl.x];
-    const int64_t poff = Ld.band[band].pix_off;
+    const int S = tl.S;
+    const int phi = tl.phi0 + threadIdx.x;
+    if ((int)threadIdx.x >= tl.nph) return;
+    const int band = Ld.seg_band[tl.first];
     const uint32_t npix = (uint32_t)Ld.band[band].npix;
+    const int64_t npt = Ld.npix_total;
+    const T *mp = maps + Ld.band[band].pix_off * (REC ? 4 : 1);
     int cur = -1;
     T mT = 0, mQ = 0, mU = 0;
-    T ghi = 0, glo = 0;
     bool bad = false;
-    auto step = [&](int64_t i, int p, int b, T dv) {
-        if (p != cur) {
-            cur = p;
-            if ((uint32_t)p < npix) {
-                const Stokes4<T> m = maps[poff + p];
-                mT = m.t;
-                mQ = m.q;
-                mU = m.u;
-            } else {
-                mT = mQ = mU = (T)NAN;
-            }
-        }
-        const cx<T> cs = tr[b & 2047];
-        if constexpr (SUB) {
-            T rv;
-            if constexpr (sizeof(T) == 4) {
-                const float pu = fmaf(mQ, cs.x, mU * cs.y);
-                rv = fmaf(-ghi, mT, dv);
-                rv = fmaf(-glo, mT, rv);
-                rv = fmaf(-ghi, pu, rv);
-            } else {
-                rv = dv - ghi * (mT + mQ * cs.x + mU * cs.y);
-            }
-            bad |= (uint32_t)p < npix && !isfinite(rv);
-            r_out[i] = rv;
-        } else {
-            r_out[i] = ghi * (mT + mQ * cs.x + mU * cs.y);
-        }
-    };
-    for (int gi = 0; gi < ngrp; ++gi) {
-        const int seg = tl.x + gi;
+    for (int gi = 0; gi < tl.ngrp; ++gi) {
+        const int seg = tl.first + gi;
         const int64_t s0 = Ld.seg_off[seg];
         const int n = (int)(Ld.seg_off[seg + 1] - s0);
         const double g = gain[seg];
-        ghi = (T)g;
-        glo = (T)(g - (double)ghi);
-        int t = phi;
-        for (; t + 3 * S < n; t += 4 * S) {
+        const T ghi = (T)g, glo = (T)(g - (double)ghi);
+        int t0;
+        const int cnt = part_visits(tl, n, rev, t0);
+        const int end = (int)min((int64_t)n, t0 + (int64_t)cnt * S);
+        auto step = [&](int64_t i, int p, int b, T dv) {
+            if (p != cur) {
+                cur = p;
+                if ((uint32_t)p < npix) {
+                    const Stokes4<T> m = map_at<REC>(mp, npt, p);
+                    mT = m.t;
+                    mQ = m.q;
+                    mU = m.u;
+                } else {
+                    mT = mQ = mU = (T)NAN;
+                }
+            }
+            const cx<T> cs = trig_at(tr, b);
+            if constexpr (SUB) {
+                T rv;
+                if constexpr (sizeof(T) == 4) {
+                    const float pu = fmaf(mQ, cs.x, mU * cs.y);
+                    rv = fmaf(-ghi, mT, dv);
+                    rv = fmaf(-glo, mT, rv);
+                    rv = fmaf(-ghi, pu, rv);
+                } else {
+                    rv = dv - ghi * (mT + mQ * cs.x + mU * cs.y);
+                }
+                bad |= (uint32_t)p < npix && !isfinite(rv);
+                r_out[i] = rv;
+            } else {
+                r_out[i] = ghi * (mT + mQ * cs.x + mU * cs.y);
+            }
+        };
+        int t = phi + t0;
+        for (; t + 3 * S < end; t += 4 * S) {
             int p[4], b[4];
             T v[4];
 #pragma unroll
@@ -267,7 +372,7 @@ __global__ __launch_bounds__(C3_NT) void k_resid(LayoutDev Ld, const int4 *__res
 #pragma unroll
             for (int u = 0; u < 4; ++u) step(s0 + t + u * S, p[u], b[u], v[u]);
         }
-        for (; t < n; t += S) {
+        for (; t < end; t += S) {
             const int64_t i = s0 + t;
             step(i, pix[i], psi[i], SUB ? (T)d[i] : (T)0);
         }
@@ -416,128 +521,101 @@ __global__ __launch_bounds__(C3_NT) void k_probe(const int32_t *__restrict__ pix
 // segment sum r^2/sigma0^2, sum (P m) r and sum r^2 (block sums, one atomic
 // each); with GRAD the map adjoint -2 g r / sigma0^2 (1, c, s) summed per
 // pixel in registers and added with FP64 atomics when the lane's pixel
-// changes, into gmap4: one 32-byte record (T, Q, U, unused) per pixel, so a
-// flush's three atomics fall on one cache line.  The thread keeps its
-// pixel's T, Q, U (interleaved records) in registers across revisits, and
-// keeps eight revisits' loads in flight (d of type TD; both types
-// compile-time, so the loads issue with no branch between).
-template <typename T, typename TD, bool GRAD>
+// changes (Sums3, wave_flush), to gmap in the maps' layout (REC: records of
+// four, else planes).  The thread keeps its pixel's T, Q, U in registers across revisits, and keeps eight
+// revisits' loads in flight (d of type TD; both types compile-time, so the
+// loads issue with no branch between).
+template <typename T, typename TD, bool GRAD, bool REC>
 __global__ __launch_bounds__(C3_NT) void k_chisq_time(
-    LayoutDev Ld, const int4 *__restrict__ tiles, const int32_t *__restrict__ pix,
+    LayoutDev Ld, const int4 *__restrict__ tiles, int rev, const int32_t *__restrict__ pix,
     const uint16_t *__restrict__ psi, const TD *__restrict__ d, const T *__restrict__ ncorr,
-    const Stokes4<T> *__restrict__ maps, const double *__restrict__ gain,
+    const T *__restrict__ maps, const double *__restrict__ gain,
     const double *__restrict__ sigma0, const cx<double> *__restrict__ trig,
-    double *__restrict__ seg_sums, double *__restrict__ gmap4, double gscale0,
+    double *__restrict__ seg_sums, double *__restrict__ gmap, double gscale0,
     const double *__restrict__ gscale_dev) {
     // dL/dJ: a host factor times an optional device scalar (read here, so the
     // caller's autograd never waits for it)
     const double gscale = gscale_dev ? gscale0 * *gscale_dev : gscale0;
-    __shared__ cx<double> tr[2048];
+    __shared__ cx<double> tr[kTrig<double>];
     __shared__ double red[3][C3_NT / 64];
-    const int4 tl = tiles[blockIdx.x];
-    for (int b = threadIdx.x; b < 2048; b += C3_NT) tr[b] = trig[b];
+    __shared__ RecLds<GRAD ? 3 : 1> recs[C3_NT / 64];
+    const Tile tl = tile_of(tiles[blockIdx.x]);
+    if (tl.nph == 0) return;  // an empty tile (launch padding)
+    trig_stage(tr, trig);
     __syncthreads();
-    const int S = tl.z;
-    const int nph = tl.w & 0xFFFF, ngrp = tl.w >> 16;
-    const int phi = tl.y + threadIdx.x;
-    const bool act = (int)threadIdx.x < nph;
-    const int band = Ld.seg_band[tl.x];
-    const int64_t poff = Ld.band[band].pix_off;
+    RecLds<GRAD ? 3 : 1> &L = recs[threadIdx.x >> 6];
+    const int S = tl.S;
+    const int phi = tl.phi0 + threadIdx.x;
+    const bool act = (int)threadIdx.x < tl.nph;
+    const int band = Ld.seg_band[tl.first];
     const uint32_t npix = (uint32_t)Ld.band[band].npix;
-    // map-adjoint sums of the current pixel and the two before it (most
-    // recent first), flushed when a fourth pixel arrives or the tile ends (as
-    // in the binning: a flush inside the loop also delays the next loads)
-    int cur = -1, old = -1, older = -1;
+    const int64_t npt = Ld.npix_total;
+    const T *mp = maps + Ld.band[band].pix_off * (REC ? 4 : 1);
+    double *gp = GRAD ? gmap + Ld.band[band].pix_off * (REC ? 4 : 1) : nullptr;
+    auto rec = [&](int p, int j) { return REC ? gp + (int64_t)p * 4 + j : gp + p + j * npt; };
+    int cur = -1;
     double mT = 0, mQ = 0, mU = 0;  // map values of pixel cur
-    double a[3] = {0, 0, 0}, o[3] = {0, 0, 0}, q[3] = {0, 0, 0};
-    double g = 0, cfac = 0, sr2 = 0, spr = 0;
-    auto flush = [&](int pp, const double *x) {
-        double *rec = gmap4 + (poff + pp) * 4;
-        atomicAdd(rec, x[0]);
-        atomicAdd(rec + 1, x[1]);
-        atomicAdd(rec + 2, x[2]);
-    };
-    auto step = [&](int p, int b, double dv, double nc) {
-        if ((uint32_t)p >= npix) return;  // out-of-range pixels are not in the likelihood
-        if (p != cur) {
-            if constexpr (GRAD) {
-                if (p == old) {
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        const double x = a[j];
-                        a[j] = o[j];
-                        o[j] = x;
-                    }
-                    old = cur;
-                } else if (p == older) {
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        const double x = q[j];
-                        q[j] = o[j];
-                        o[j] = a[j];
-                        a[j] = x;
-                    }
-                    older = old;
-                    old = cur;
-                } else {
-                    if (older >= 0) flush(older, q);
-#pragma unroll
-                    for (int j = 0; j < 3; ++j) {
-                        q[j] = o[j];
-                        o[j] = a[j];
-                        a[j] = 0.0;
-                    }
-                    older = old;
-                    old = cur;
-                }
-            }
-            cur = p;
-            const Stokes4<T> m = maps[poff + p];
-            mT = m.t;
-            mQ = m.q;
-            mU = m.u;
-        }
-        const cx<double> cs = tr[b & 2047];
-        const double Pm = mT + mQ * cs.x + mU * cs.y;
-        const double r = dv - g * Pm - nc;
-        sr2 += r * r;
-        spr += Pm * r;
-        if constexpr (GRAD) {
-            const double cr = cfac * r;
-            a[0] += cr;
-            a[1] += cr * cs.x;
-            a[2] += cr * cs.y;
-        }
-    };
-    for (int gi = 0; gi < ngrp; ++gi) {
-        const int seg = tl.x + gi;
+    Sums3<GRAD ? 3 : 1> s3;
+    s3.clear();
+    for (int gi = 0; gi < tl.ngrp; ++gi) {
+        const int seg = tl.first + gi;
         if (Ld.seg_accept && !Ld.seg_accept[seg]) continue;  // uniform over the block
         const int64_t s0 = Ld.seg_off[seg];
         const int n = (int)(Ld.seg_off[seg + 1] - s0);
-        g = gain[seg];
+        const double g = gain[seg];
         const double sg = sigma0[seg];
         const double is2 = 1.0 / (sg * sg);
-        cfac = -2.0 * g * is2 * gscale;
-        sr2 = spr = 0;
-        int t = act ? phi : n;
-        for (; t + 7 * S < n; t += 8 * S) {  // eight revisits' loads in flight
+        const double cfac = -2.0 * g * is2 * gscale;
+        double sr2 = 0, spr = 0;
+        int t0;
+        const int cnt = part_visits(tl, n, rev, t0);
+        if (cnt == 0) continue;  // uniform over the block
+        const int32_t *pixs = pix + s0;
+        const uint16_t *psis = psi + s0;
+        const TD *ds = d + s0;
+        const T *ns = ncorr + s0;
+        int t = phi + t0;
+        for (int u0 = 0; u0 < cnt; u0 += 8, t += 8 * S) {  // eight revisits' loads in flight
             int p[8], b[8];
             TD v[8];
             T c[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                const int64_t i = s0 + t + u * S;
-                p[u] = pix[i];
-                b[u] = psi[i];
-                v[u] = d[i];
-                c[u] = ncorr[i];
+                const uint32_t i = (uint32_t)min(t + u * S, n - 1);
+                p[u] = at(pixs, i);
+                b[u] = at(psis, i);
+                v[u] = at(ds, i);
+                c[u] = at(ns, i);
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) step(p[u], b[u], (double)v[u], (double)c[u]);
-        }
-        for (; t < n; t += S) {
-            const int64_t i = s0 + t;
-            step(pix[i], psi[i], (double)d[i], (double)ncorr[i]);
+            for (int u = 0; u < 8; ++u) {
+                // out-of-range pixels are not in the likelihood
+                const bool ok = act && t + u * S < n && (uint32_t)p[u] < npix;
+                const bool ev = ok && p[u] != cur;
+                if constexpr (GRAD) {
+                    if (__ballot(ev)) s3.move(L, ev, p[u], rec);
+                }
+                if (ev) {
+                    cur = p[u];
+                    const Stokes4<T> m = map_at<REC>(mp, npt, cur);
+                    mT = m.t;
+                    mQ = m.q;
+                    mU = m.u;
+                }
+                if (ok) {
+                    const cx<double> cs = trig_at(tr, b[u]);
+                    const double Pm = mT + mQ * cs.x + mU * cs.y;
+                    const double r = (double)v[u] - g * Pm - (double)c[u];
+                    sr2 += r * r;
+                    spr += Pm * r;
+                    if constexpr (GRAD) {
+                        const double cr = cfac * r;
+                        s3.a[0] += cr;
+                        s3.a[1] += cr * cs.x;
+                        s3.a[2] += cr * cs.y;
+                    }
+                }
+            }
         }
         // per-segment sums: block reduction, one atomic per sum
         double v[3] = {sr2 * is2, spr, sr2};
@@ -554,11 +632,7 @@ __global__ __launch_bounds__(C3_NT) void k_chisq_time(
         }
         __syncthreads();
     }
-    if constexpr (GRAD) {
-        if (cur >= 0) flush(cur, a);
-        if (old >= 0) flush(old, o);
-        if (older >= 0) flush(older, q);
-    }
+    if constexpr (GRAD) s3.finish(L, rec);
 }
 
 __global__ __launch_bounds__(C3_NT) void k_chisq_finish(
@@ -588,7 +662,7 @@ __global__ __launch_bounds__(C3_NT) void k_chisq_finish(
 // the launchers pick the instantiation here
 
 template <typename TN>
-void launch_bin_typed(hipStream_t st, const LayoutDev &L, const int4 *tiles, int ntile, const int2 *runs,
+void launch_bin_typed(hipStream_t st, const LayoutDev &L, const int4 *tiles, int ntile, int rev, const int2 *runs,
                       const int32_t *pix,
                       const uint16_t *psi, const void *d, int d_f64, const TN *nc, const double *gain,
                       const double *sigma0, const cx<double> *tr, double *acc, uint32_t *err) {
@@ -596,67 +670,64 @@ void launch_bin_typed(hipStream_t st, const LayoutDev &L, const int4 *tiles, int
     if (d_f64) {
         const double *dd = (const double *)d;
         if (nc)
-            hipLaunchKernelGGL((k_bin<TN, double, true>), g, b, 0, st, L, tiles, runs, pix, psi, dd, nc, gain, sigma0,
+            hipLaunchKernelGGL((k_bin<TN, double, true>), g, b, 0, st, L, tiles, rev, runs, pix, psi, dd, nc, gain, sigma0,
                                tr, acc, err);
         else
-            hipLaunchKernelGGL((k_bin<TN, double, false>), g, b, 0, st, L, tiles, runs, pix, psi, dd, nc, gain, sigma0,
+            hipLaunchKernelGGL((k_bin<TN, double, false>), g, b, 0, st, L, tiles, rev, runs, pix, psi, dd, nc, gain, sigma0,
                                tr, acc, err);
     } else {
         const float *df = (const float *)d;
         if (nc)
-            hipLaunchKernelGGL((k_bin<TN, float, true>), g, b, 0, st, L, tiles, runs, pix, psi, df, nc, gain, sigma0,
+            hipLaunchKernelGGL((k_bin<TN, float, true>), g, b, 0, st, L, tiles, rev, runs, pix, psi, df, nc, gain, sigma0,
                                tr, acc, err);
         else
-            hipLaunchKernelGGL((k_bin<TN, float, false>), g, b, 0, st, L, tiles, runs, pix, psi, df, nc, gain, sigma0,
+            hipLaunchKernelGGL((k_bin<TN, float, false>), g, b, 0, st, L, tiles, rev, runs, pix, psi, df, nc, gain, sigma0,
                                tr, acc, err);
     }
 }
 
-// maps -> interleaved records, then s = g P m (d == NULL) or r = d - g P m
+// maps -> records of four values in maps4
 template <typename T>
-void launch_resid_typed(hipStream_t st, const LayoutDev &L, const int4 *tiles, int ntile, const int32_t *pix,
-                        const uint16_t *psi, const void *d, int d_f64, const void *maps, void *maps4,
-                        const double *gain, const void *trig, void *r_out, uint32_t *err) {
-    const int64_t npt = L.npix_total;
+void launch_interleave(hipStream_t st, int64_t npt, const void *maps, void *maps4) {
     const int gi = (int)std::min<int64_t>((npt + C3_NT - 1) / C3_NT, 65536);
     hipLaunchKernelGGL(k_interleave<T>, dim3(gi), dim3(C3_NT), 0, st, (const T *)maps, npt, (Stokes4<T> *)maps4);
-    const Stokes4<T> *m4 = (const Stokes4<T> *)maps4;
-    const cx<T> *tr = (const cx<T> *)trig;
-    T *out = (T *)r_out;
-    const dim3 g(ntile), b(C3_NT);
-    if (!d)
-        hipLaunchKernelGGL((k_resid<T, T, false>), g, b, 0, st, L, tiles, pix, psi, (const T *)nullptr, m4, gain,
-                           tr, out, err);
-    else if (d_f64)
-        hipLaunchKernelGGL((k_resid<T, double, true>), g, b, 0, st, L, tiles, pix, psi, (const double *)d, m4,
-                           gain, tr, out, err);
-    else
-        hipLaunchKernelGGL((k_resid<T, float, true>), g, b, 0, st, L, tiles, pix, psi, (const float *)d, m4,
-                           gain, tr, out, err);
 }
 
-template <typename T>
-void launch_chisq_typed(hipStream_t st, const LayoutDev &L, const int4 *tiles, int ntile, const int32_t *pix,
-                        const uint16_t *psi, const void *d, int d_f64, const void *ncorr, const void *maps,
-                        void *maps4, const double *gain, const double *sigma0, const void *trig64,
-                        double *seg_sums, double *grad_maps4, double grad_scale, const double *gscale_dev) {
-    const int64_t npt = L.npix_total;
-    const int gi = (int)std::min<int64_t>((npt + C3_NT - 1) / C3_NT, 65536);
-    hipLaunchKernelGGL(k_interleave<T>, dim3(gi), dim3(C3_NT), 0, st, (const T *)maps, npt, (Stokes4<T> *)maps4);
-    const Stokes4<T> *m4 = (const Stokes4<T> *)maps4;
-    const T *nc = (const T *)ncorr;
-    const cx<double> *tr = (const cx<double> *)trig64;
+// s = g P m (d == NULL) or r = d - g P m; m: the maps, or their records (REC)
+template <typename T, bool REC>
+void launch_resid_typed(hipStream_t st, const LayoutDev &L, const int4 *tiles, int ntile, int rev, const int32_t *pix,
+                        const uint16_t *psi, const void *d, int d_f64, const void *m, const double *gain,
+                        const void *trig, void *r_out, uint32_t *err) {
     const dim3 g(ntile), b(C3_NT);
-#define C3_CHISQ(TD, GRAD)                                                                              \
-    hipLaunchKernelGGL((k_chisq_time<T, TD, GRAD>), g, b, 0, st, L, tiles, pix, psi, (const TD *)d, nc, m4, \
-                       gain, sigma0, tr, seg_sums, grad_maps4, grad_scale, gscale_dev)
+#define C3_RESID(TD, SUB)                                                                                     \
+    hipLaunchKernelGGL((k_resid<T, TD, SUB, REC>), g, b, 0, st, L, tiles, rev, pix, psi, (const TD *)d, (const T *)m, \
+                       gain, (const cx<T> *)trig, (T *)r_out, err)
+    if (!d)
+        C3_RESID(T, false);
+    else if (d_f64)
+        C3_RESID(double, true);
+    else
+        C3_RESID(float, true);
+#undef C3_RESID
+}
+
+template <typename T, bool REC>
+void launch_chisq_typed(hipStream_t st, const LayoutDev &L, const int4 *tiles, int ntile, int rev,
+                        const int32_t *pix, const uint16_t *psi, const void *d, int d_f64, const void *ncorr,
+                        const void *m, const double *gain, const double *sigma0, const void *trig64,
+                        double *seg_sums, double *gmap, double grad_scale, const double *gscale_dev) {
+    const dim3 g(ntile), b(C3_NT);
+#define C3_CHISQ(TD, GRAD)                                                                                   \
+    hipLaunchKernelGGL((k_chisq_time<T, TD, GRAD, REC>), g, b, 0, st, L, tiles, rev, pix, psi, (const TD *)d, \
+                       (const T *)ncorr, (const T *)m, gain, sigma0, (const cx<double> *)trig64, seg_sums, gmap, \
+                       grad_scale, gscale_dev)
     if (d_f64) {
-        if (grad_maps4)
+        if (gmap)
             C3_CHISQ(double, true);
         else
             C3_CHISQ(double, false);
     } else {
-        if (grad_maps4)
+        if (gmap)
             C3_CHISQ(float, true);
         else
             C3_CHISQ(float, false);
@@ -669,28 +740,37 @@ void launch_chisq_typed(hipStream_t st, const LayoutDev &L, const int4 *tiles, i
 namespace c3 {
 
 hipError_t launch_bin_tiles(hipStream_t st, const LayoutDev &L, int mixed, const int4 *tiles,
-                            int ntile, const int2 *runs, const int32_t *pix, const uint16_t *psi,
+                            int ntile, int rev, const int2 *runs, const int32_t *pix, const uint16_t *psi,
                             const void *d, int d_f64, const void *ncorr, const double *gain,
                             const double *sigma0, const void *trig64, double *acc, uint32_t *err) {
     if (ntile <= 0) return hipSuccess;
     if (mixed)
-        launch_bin_typed(st, L, tiles, ntile, runs, pix, psi, d, d_f64, (const float *)ncorr, gain, sigma0,
+        launch_bin_typed(st, L, tiles, ntile, rev, runs, pix, psi, d, d_f64, (const float *)ncorr, gain, sigma0,
                          (const cx<double> *)trig64, acc, err);
     else
-        launch_bin_typed(st, L, tiles, ntile, runs, pix, psi, d, d_f64, (const double *)ncorr, gain, sigma0,
+        launch_bin_typed(st, L, tiles, ntile, rev, runs, pix, psi, d, d_f64, (const double *)ncorr, gain, sigma0,
                          (const cx<double> *)trig64, acc, err);
     return hipGetLastError();
 }
 
 hipError_t launch_resid_tiles(hipStream_t st, const LayoutDev &L, int mixed, const int4 *tiles,
-                              int ntile, const int32_t *pix, const uint16_t *psi, const void *d,
+                              int ntile, int rev, const int32_t *pix, const uint16_t *psi, const void *d,
                               int d_f64, const void *maps, void *maps4, const double *gain,
                               const void *trig, void *r_out, uint32_t *err) {
     if (ntile <= 0) return hipSuccess;
+    auto go = [&](auto zero) {
+        using T = decltype(zero);
+        if (maps4) {
+            launch_interleave<T>(st, L.npix_total, maps, maps4);
+            launch_resid_typed<T, true>(st, L, tiles, ntile, rev, pix, psi, d, d_f64, maps4, gain, trig, r_out, err);
+        } else {
+            launch_resid_typed<T, false>(st, L, tiles, ntile, rev, pix, psi, d, d_f64, maps, gain, trig, r_out, err);
+        }
+    };
     if (mixed)
-        launch_resid_typed<float>(st, L, tiles, ntile, pix, psi, d, d_f64, maps, maps4, gain, trig, r_out, err);
+        go(0.0f);
     else
-        launch_resid_typed<double>(st, L, tiles, ntile, pix, psi, d, d_f64, maps, maps4, gain, trig, r_out, err);
+        go(0.0);
     return hipGetLastError();
 }
 
@@ -742,18 +822,27 @@ hipError_t launch_repeat_probe(hipStream_t st, const int32_t *pix, int64_t off, 
 }
 
 hipError_t launch_chisq_time_tiles(hipStream_t st, const LayoutDev &L, int mixed, const int4 *tiles,
-                                   int ntile, const int32_t *pix, const uint16_t *psi,
+                                   int ntile, int rev, const int32_t *pix, const uint16_t *psi,
                                    const void *d, int d_f64, const void *ncorr, const void *maps,
                                    void *maps4, const double *gain, const double *sigma0,
-                                   const void *trig64, double *seg_sums, double *grad_maps4,
+                                   const void *trig64, double *seg_sums, double *gmap,
                                    double grad_scale, const double *gscale_dev) {
     if (ntile <= 0) return hipSuccess;
+    auto go = [&](auto zero) {
+        using T = decltype(zero);
+        if (maps4) {
+            launch_interleave<T>(st, L.npix_total, maps, maps4);
+            launch_chisq_typed<T, true>(st, L, tiles, ntile, rev, pix, psi, d, d_f64, ncorr, maps4, gain, sigma0,
+                                        trig64, seg_sums, gmap, grad_scale, gscale_dev);
+        } else {
+            launch_chisq_typed<T, false>(st, L, tiles, ntile, rev, pix, psi, d, d_f64, ncorr, maps, gain, sigma0,
+                                         trig64, seg_sums, gmap, grad_scale, gscale_dev);
+        }
+    };
     if (mixed)
-        launch_chisq_typed<float>(st, L, tiles, ntile, pix, psi, d, d_f64, ncorr, maps, maps4, gain, sigma0,
-                                  trig64, seg_sums, grad_maps4, grad_scale, gscale_dev);
+        go(0.0f);
     else
-        launch_chisq_typed<double>(st, L, tiles, ntile, pix, psi, d, d_f64, ncorr, maps, maps4, gain, sigma0,
-                                   trig64, seg_sums, grad_maps4, grad_scale, gscale_dev);
+        go(0.0);
     return hipGetLastError();
 }
 
