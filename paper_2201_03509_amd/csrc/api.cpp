@@ -244,6 +244,8 @@ HuffDev make_huff_dev(const tod_huff *h) {
     d.seg_chunk_off = h->seg_chunk_off;
     d.chunk_len = h->chunk_len;
     d.ntable = h->ntable;
+    d.nwords = h->nwords;
+    d.nchunk = h->nchunk;
     return d;
 }
 

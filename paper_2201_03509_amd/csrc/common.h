@@ -143,6 +143,7 @@ struct HuffDev {
     const int64_t *seg_chunk_off;
     int32_t chunk_len;
     int32_t ntable;
+    int64_t nwords, nchunk;
 };
 
 // Canonical decoding table of one Huffman table blob, built on the device per

@@ -1,7 +1,7 @@
 // Huffman decode + undifferencing of the pointing streams (section 4.1), and
 // of the TOD and flag streams (k_decode1: one stream, same format).
 //
-// Two kernels per call.
+// Two kernels per call: k_tables, then a decoder.
 //
 // k_tables turns every table blob into a DecTab: the canonical limits and a
 // 12-bit prefix table giving the code length of every prefix whose codes all
@@ -12,12 +12,18 @@
 // than 12 bits); only codes behind one of the <= 20 split prefixes search the
 // limits.
 //
+// The decoders: k_decode32 and k_decode32_1 for chunks of 32 symbols (the
+// default spacing of the side index), k_decode and k_decode1 for longer
+// chunks, whose words would not fit a block's LDS, and for streams of 32-symbol
+// chunks too dense for it (over 23 bits a sample for the pointing).
+//
 // k_decode: a block owns up to C3_DEC_NT consecutive chunks of one segment; each
 // thread parses one chunk of both streams from the side index, G codes per
 // round, adds the symbol values to its running value (x_i = x_{i-1} + d_i),
 // range-checks, and leaves the samples in an LDS tile; the block then writes
 // the tile in rows of 16 consecutive samples of a chunk.
 #include <mutex>
+#include <type_traits>
 
 #include "common.h"
 
@@ -44,62 +50,86 @@ __device__ __forceinline__ int resolve_len(const DecTab &T, uint32_t win, int e)
     return code_len(T, win, e ? (e & 63) : T.minlen);
 }
 
-__global__ __launch_bounds__(C3_NT) void k_tables(HuffDev hp, HuffDev hs, DecTab *tabs) {
-    __shared__ DecTab T;
-    const int b = blockIdx.x;
-    const bool is_p = b < hp.ntable;
-    const uint32_t *tables = is_p ? hp.tables : hs.tables;
-    const int64_t *table_off = is_p ? hp.table_off : hs.table_off;
-    const int t = is_p ? b : b - hp.ntable;
-    const uint32_t *blob = tables + table_off[t];
-    if (threadIdx.x == 0) {
-        // blob: [nsym, maxlen, count_1 .. count_32, symbols...]
-        unsigned long long first = 0;
+// The decoding table of one blob [nsym, maxlen, count_1 .. count_32, symbols...]
+// in LDS, by all NT threads of a block; they meet at a barrier at its end.  The
+// 32 counts are loaded by 32 lanes at once and walked in registers, and a
+// prefix's two lengths are counts of the limits below it, so nothing in it is
+// a chain of loads (one thread walking the blob, and a search per prefix, took
+// 14 to 27 us a call: more than the decode itself for a few scans).
+template <int NT>
+__device__ __forceinline__ void build_table(DecTab &T, const uint32_t *__restrict__ blob) {
+    const int tid = threadIdx.x;
+    if (tid < 64) {
+        const uint32_t mine = tid >= 1 && tid <= 32 ? blob[1 + tid] : 0;
+        unsigned long long first = 0, lim = 0;
         int64_t off = 0;
-        int ok = 1;
-        T.minlen = 33;
-        T.maxlen = 0;
+        int32_t delta = 0;
+        int ok = 1, minlen = 33, maxlen = 0;
         for (int L = 1; L <= 32; ++L) {
-            const uint32_t cnt = blob[1 + L];
-            T.delta[L] = (int32_t)(off - (int64_t)first);
+            const uint32_t cnt = __builtin_amdgcn_readlane(mine, L);
             const unsigned long long end = first + cnt;
             if (end > (1ull << L)) ok = 0;  // more codes of length <= L than L bits hold
-            T.lim[L] = end << (32 - L);
+            if (tid == L) {
+                delta = (int32_t)(off - (int64_t)first);
+                lim = end << (32 - L);
+            }
+            if (tid == 33) lim = end << (32 - L);  // ends as lim[32]
             if (cnt) {
-                if (T.minlen > 32) T.minlen = L;
-                T.maxlen = L;
+                if (minlen > 32) minlen = L;
+                maxlen = L;
             }
             off += cnt;
             first = end << 1;
         }
-        T.lim[0] = 0;
-        T.delta[0] = 0;
-        T.lim[33] = T.lim[32];
-        T.delta[33] = 0;
-        if (T.maxlen == 0 || off != (int64_t)blob[0]) ok = 0;
-        if (T.minlen > 32) T.minlen = 32;
-        T.nsym = ok ? (int32_t)off : 0;
-        T.ok = ok;
-        T.pad[0] = T.pad[1] = 0;
-    }
-    __syncthreads();
-    for (int e = threadIdx.x; e < (1 << C3_KLUT); e += C3_NT) {
-        uint8_t v = 0;
-        if (T.ok) {
-            // code lengths only grow with the code value, so the prefix's
-            // codes have lengths from L0 (its first) to L1 (its last)
-            const unsigned long long w0 = (unsigned long long)e << SPLIT;
-            const unsigned long long w1 = w0 | ((1ull << SPLIT) - 1);
-            const int L0 = code_len(T, w0);
-            const int L1 = code_len(T, w1);
-            v = L0 == 0 ? 0 : (uint8_t)(L0 == L1 ? L0 : 64 | L0);
+        if (maxlen == 0 || off != (int64_t)blob[0]) ok = 0;
+        if (tid <= 33) {
+            T.lim[tid] = lim;
+            T.delta[tid] = delta;
         }
-        T.lut[e] = v;
+        if (tid == 0) {
+            T.minlen = minlen > 32 ? 32 : minlen;
+            T.maxlen = maxlen;
+            T.nsym = ok ? (int32_t)off : 0;
+            T.ok = ok;
+            T.pad[0] = T.pad[1] = 0;
+        }
     }
     __syncthreads();
+    // Code lengths only grow with the code value, so a prefix's codes have
+    // lengths from L0 (its first code's) to L1 (its last code's); the limits
+    // grow with the length, so each is minlen plus the limits passed.
+    constexpr int PER = (1 << C3_KLUT) / NT;
+    static_assert(PER * NT == 1 << C3_KLUT, "prefixes per thread");
+    const int e0 = tid * PER;
+    const int lo = T.minlen, hi = T.maxlen;
+    int n0[PER], n1[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) n0[i] = n1[i] = lo;
+    for (int L = lo; L <= hi; ++L) {
+        const unsigned long long lim = T.lim[L];
+        const int c = (int)((lim + ((1ull << SPLIT) - 1)) >> SPLIT), f = (int)(lim >> SPLIT);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            n0[i] += e0 + i >= c;
+            n1[i] += e0 + i >= f;
+        }
+    }
+    const bool ok = T.ok;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        T.lut[e0 + i] = !ok || n0[i] > hi ? 0 : (uint8_t)(n0[i] == n1[i] ? n0[i] : 64 | n0[i]);
+    __syncthreads();
+}
+
+__global__ __launch_bounds__(1024) void k_tables(HuffDev hp, HuffDev hs, DecTab *tabs) {
+    __shared__ DecTab T;
+    const int b = blockIdx.x;
+    const bool is_p = b < hp.ntable;
+    const int t = is_p ? b : b - hp.ntable;
+    build_table<1024>(T, is_p ? hp.tables + hp.table_off[t] : hs.tables + hs.table_off[t]);
     const uint4 *src = (const uint4 *)&T;
     uint4 *dst = (uint4 *)(tabs + b);
-    for (int i = threadIdx.x; i < (int)(sizeof(DecTab) / 16); i += C3_NT) dst[i] = src[i];
+    for (int i = threadIdx.x; i < (int)(sizeof(DecTab) / 16); i += 1024) dst[i] = src[i];
 }
 
 // word 3 of a raw buffer resource on gfx9-family chips (untyped dword access)
@@ -376,6 +406,586 @@ __global__ __launch_bounds__(C3_DEC_NT) void k_decode(LayoutDev Ld, HuffDev hp, 
     if (tid == 0 && blk_err) atomicOr(err, blk_err);
 }
 
+// ------------------------------------------- chunks of 32 symbols, words in LDS
+// The decoders for the densest side index (chunk_len = 32, the format's
+// default).  Everything a lane's serial code chain reads is in LDS: the
+// block's stream words (staged with coalesced loads; its 512 chunks are
+// consecutive in the stream), the decoding tables and the symbol values as
+// 16-bit integers, most frequent first.  The window of the next 32 bits is one
+// two-word LDS read at the lane's bit position, so there is no look-ahead
+// state, and a lane writes its own 32 consecutive samples straight from
+// registers in 16-byte stores: no LDS tile, no barrier after the staging.
+// Symbols that do not fit (beyond the table's first KS entries, or wider than
+// 16 bits) are marked and read from memory, eight codes' together.
+//
+// The decoder that gathers its symbols from memory and reads its words per
+// lane is bound by the texture path (64 cache lines per gather); this one by
+// the code chain (LDS latency, then vector-ALU issue at 0.45).  Pointing, 70
+// GHz-like: 9.4e8 samples 5.32 -> 3.20 ms, 1e8 samples 611 -> 356 us; pointing,
+// TOD and flags of a 30 GHz-like set of 1.8e7 samples 314 -> 212 us (tables
+// included).
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+struct __attribute__((packed, aligned(4))) Store16 {
+    u32x4 v;
+};
+struct __attribute__((packed, aligned(2))) Store16h {
+    u32x4 v;
+};
+struct __attribute__((packed, aligned(1))) Store16b {
+    u32x4 v;
+};
+
+constexpr int kEsc = -32768;      // marks a symbol that is read from memory
+constexpr int kWordsPer = 36;     // words a chunk may touch from its first on: 32 codes of 32 bits, and a window's three
+
+// LDS image of one stream: table, 16-bit symbols (two extra entries: the
+// escape, and the zero that an invalid code yields), staged words
+template <int KS>
+struct StreamLds {
+    DecTab T;
+    int16_t sym[KS + 2];
+};
+
+// Staging, in two halves so that every load of a block is issued before the
+// first is waited for: PER dwords a thread, 512 apart, from a raw buffer
+// (zeros past its end), then to LDS.
+template <int PER>
+struct Stage {
+    uint32_t v[PER];
+    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, uint32_t w0) {
+#pragma unroll
+        for (int r = 0; r < PER; ++r) v[r] = buf_word(rs, w0 + threadIdx.x + (uint32_t)r * C3_DEC_NT);
+    }
+    __device__ __forceinline__ void words(uint32_t *W, uint32_t n) const {
+#pragma unroll
+        for (int r = 0; r < PER; ++r)
+            if (threadIdx.x + (uint32_t)r * C3_DEC_NT < n) W[threadIdx.x + r * C3_DEC_NT] = v[r];
+    }
+    // as symbols: 16-bit values, or the escape
+    template <int KS>
+    __device__ __forceinline__ void symbols(StreamLds<KS> &S) const {
+        static_assert(KS == PER * C3_DEC_NT, "symbols per thread");
+#pragma unroll
+        for (int r = 0; r < PER; ++r) {
+            const int x = (int)v[r];
+            S.sym[threadIdx.x + r * C3_DEC_NT] = (int16_t)(x > kEsc && x <= 32767 ? x : kEsc);
+        }
+        if (threadIdx.x == 0) {
+            S.sym[KS] = (int16_t)kEsc;
+            S.sym[KS + 1] = 0;
+        }
+    }
+};
+// words beyond the first 16 of a thread
+__device__ __forceinline__ void stage_rest(uint32_t *W, __amdgpu_buffer_rsrc_t rs, uint32_t w0, uint32_t n) {
+    for (uint32_t i = threadIdx.x + 16 * C3_DEC_NT; i < n; i += C3_DEC_NT) W[i] = buf_word(rs, w0 + i);
+}
+// a table's symbols as a raw buffer: those its blob has room for
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t symbol_buffer(const HuffDev &h, int t) {
+    const uint32_t *blob = h.tables + h.table_off[t];
+    const int64_t room = max((int64_t)0, min(h.table_off[t + 1] - h.table_off[t] - 34, (int64_t)blob[0]));
+    return raw_buffer(blob + 34, (int32_t)(4 * min(room, (int64_t)1 << 28)));
+}
+
+// One stream of one lane: bit position (relative to the staged words, or to
+// the segment's stream when they are not staged) and running value.
+template <int KS, bool STAGED>
+struct LaneStream {
+    const StreamLds<KS> &S;
+    const uint32_t *W;
+    __amdgpu_buffer_rsrc_t rs, rsym;
+    uint32_t pos;
+    int32_t x;
+    uint32_t w[3];   // the words under pos and the two after them
+    uint32_t at;     // bit within them
+    int L;           // length of the current code
+    bool inv;        // no code matches: one bit is consumed, the symbol counts as 0
+
+    // one read serves two codes: 31 + 32 + 32 bits at most
+    __device__ __forceinline__ void read() {
+        const uint32_t i = pos >> 5;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) w[k] = STAGED ? W[i + k] : buf_word(rs, i + k);
+        at = pos & 31;
+    }
+    __device__ __forceinline__ uint32_t window() const {
+        const bool up = at >= 32;
+        const uint32_t a = up ? w[1] : w[0], b = up ? w[2] : w[1];
+        return (uint32_t)(((((unsigned long long)a << 32) | b) << (at & 31)) >> 32);
+    }
+    // the prefix does not settle the length: search the limits
+    __device__ __forceinline__ void search(uint32_t win, int e) {
+        L = resolve_len(S.T, win, e);
+        inv = L == 0;
+        L = inv ? 1 : L;
+    }
+    __device__ __forceinline__ uint32_t index(uint32_t win) const {
+        return (win >> (32 - L)) + (uint32_t)S.T.delta[L];
+    }
+    // the zero entry for no code, the escape beyond the symbols held
+    __device__ __forceinline__ int value(uint32_t i) const { return S.sym[inv ? KS + 1 : min(i, (uint32_t)KS)]; }
+    __device__ __forceinline__ void consume() {
+        pos += L;
+        at += L;
+    }
+};
+
+// entry e of the prefix table settles the code length
+__device__ __forceinline__ bool settled(int e) { return (uint32_t)(e - 1) < 63u; }
+
+// the marked symbols of eight codes, their reads in flight together (idx: the
+// symbols' own indices)
+template <typename LS>
+__device__ __forceinline__ void escapes(const LS &s, int *v, const uint32_t *idx) {
+    bool any = false;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) any |= v[k] == kEsc;
+    if (any) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (v[k] == kEsc) v[k] = (int)buf_word(s.rsym, idx[k]);
+    }
+}
+
+// A wave's 64 lanes each hold 16 consecutive dwords of their own output (four
+// units of 16 bytes); the transposed store makes the four rows of 16 lanes
+// write the four units of one lane, so an instruction covers whole 64-byte
+// pieces and a wave's few instructions a contiguous stretch of memory.  Lanes
+// that store their own units one by one leave 32,768 lines per XCD half
+// written, more than its L2 holds, and memory sees 2.3 times the bytes.
+// v: the units' dwords; out: the wave's first output; per: bytes of a lane's
+// output; off: offset of these units in it.
+template <typename St>
+__device__ __forceinline__ void store_rows(uint32_t *v, char *out, uint32_t per, uint32_t off) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {  // dword i of the units 0..3
+        uint32_t &a = v[i], &b = v[4 + i], &c = v[8 + i], &d = v[12 + i];
+        // rows 2, 3 of the first with rows 0, 1 of the second
+        auto x = __builtin_amdgcn_permlane32_swap(a, c, false, false);
+        auto y = __builtin_amdgcn_permlane32_swap(b, d, false, false);
+        // odd rows of the first with even rows of the second
+        auto p = __builtin_amdgcn_permlane16_swap(x[0], y[0], false, false);
+        auto q = __builtin_amdgcn_permlane16_swap(x[1], y[1], false, false);
+        a = p[0];
+        b = p[1];
+        c = q[0];
+        d = q[1];
+    }
+    const uint32_t row = (threadIdx.x >> 4) & 3, l = threadIdx.x & 15;
+    char *o = out + l * per + row * 16 + off;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+        ((St *)(o + (uint32_t)r * 16 * per))->v = u32x4{v[4 * r], v[4 * r + 1], v[4 * r + 2], v[4 * r + 3]};
+}
+
+// Dynamic LDS of the two kernels: streams, then the staged words.  Two blocks
+// of the pointing decoder share a CU, three of the single-stream decoder.
+constexpr int KSP = 4096, KSQ = 8192;  // symbols held: pixel stream, psi (and TOD, flag) stream
+constexpr int kPair = (int)(sizeof(StreamLds<KSP>) + sizeof(StreamLds<KSQ>)), kOne = (int)sizeof(StreamLds<KSQ>);
+// (LDS is allocated in units of 1280 bytes; 256 are the block votes'.)
+constexpr int kPairLds = C3_LDS_MAX / 2 - 256, kOneLds = C3_LDS_MAX / 3 / 1280 * 1280 - 256;
+constexpr uint32_t kPairWords = (kPairLds - (kPair + 15) / 16 * 16) / 4, kOneWords = (kOneLds - (kOne + 15) / 16 * 16) / 4;
+
+extern __shared__ __attribute__((aligned(16))) unsigned char c3_dec_lds[];
+
+// a table that k_tables made to LDS (blocks that build their own tables were
+// no faster at any size, one launch less included)
+template <int KS>
+__device__ __forceinline__ void stage_table(StreamLds<KS> &S, const DecTab *tab) {
+    constexpr int n = (int)(sizeof(DecTab) / 16);
+    static_assert(n <= C3_DEC_NT, "one load a thread");
+    if (threadIdx.x < n) ((uint4 *)&S.T)[threadIdx.x] = ((const uint4 *)tab)[threadIdx.x];
+}
+
+// first and last bit of the block's chunks in one stream, and whether every
+// lane's chunk lies between them (a side index in order)
+struct Span {
+    uint32_t w0, n;  // first word, words to stage
+};
+__device__ __forceinline__ Span span_of(uint32_t first, uint32_t last) {
+    const uint32_t w0 = first >> 5;
+    return Span{w0, last >= first ? (last >> 5) - w0 + kWordsPer : 0xFFFFFFFFu};
+}
+
+__global__ __launch_bounds__(C3_DEC_NT, 4) void k_decode32(LayoutDev Ld, HuffDev hp, HuffDev hs,
+                                                        const DecTab *__restrict__ tabs,
+                                                        const DecodeTask *__restrict__ tasks,
+                                                        int32_t *__restrict__ pix_out,
+                                                        uint16_t *__restrict__ psi_out, uint32_t *err) {
+    StreamLds<KSP> &SP = *(StreamLds<KSP> *)c3_dec_lds;
+    StreamLds<KSQ> &SQ = *(StreamLds<KSQ> *)(c3_dec_lds + sizeof(StreamLds<KSP>));
+    uint32_t *W = (uint32_t *)(c3_dec_lds + (kPair + 15) / 16 * 16);
+    constexpr int C = 32;
+
+    const DecodeTask task = tasks[blockIdx.x];
+    const int seg = task.seg;
+    const int64_t s0 = Ld.seg_off[seg];
+    const int n = (int)(Ld.seg_off[seg + 1] - s0);
+    const int band = Ld.seg_band[seg];
+    const uint32_t npix = (uint32_t)Ld.band[band].npix;
+    const uint32_t npsi = (uint32_t)Ld.band[band].npsi;
+    const int tpi = hp.seg_table[seg], tqi = hs.seg_table[seg];
+    const bool tabs_ok = tpi >= 0 && tpi < hp.ntable && tqi >= 0 && tqi < hs.ntable;
+    const uint32_t *bp = hp.tables + hp.table_off[tabs_ok ? tpi : 0], *bq = hs.tables + hs.table_off[tabs_ok ? tqi : 0];
+    const int64_t cp0 = hp.seg_chunk_off[seg], cq0 = hs.seg_chunk_off[seg];
+    // the side index must hold ceil(n / C) chunks for this segment
+    const int nch_idx = (int)min(hp.seg_chunk_off[seg + 1] - cp0, hs.seg_chunk_off[seg + 1] - cq0);
+    const int64_t wp0 = hp.seg_word_off[seg], wq0 = hs.seg_word_off[seg];
+    const int64_t nwp = hp.seg_word_off[seg + 1] - wp0, nwq = hs.seg_word_off[seg + 1] - wq0;
+    const bool words_ok = nwp >= 0 && nwq >= 0 && nwp < (1ll << 29) && nwq < (1ll << 29);
+    const __amdgpu_buffer_rsrc_t rsp = raw_buffer(hp.words + wp0, words_ok ? (int32_t)(4 * nwp) : 0);
+    const __amdgpu_buffer_rsrc_t rsq = raw_buffer(hs.words + wq0, words_ok ? (int32_t)(4 * nwq) : 0);
+
+    const int l = threadIdx.x;
+    const int c = task.chunk0 + l;
+    const bool active = l < task.nchunk && c < nch_idx;
+    const int nact = min(task.nchunk, nch_idx - task.chunk0);  // the block's chunks with an index entry
+    const __amdgpu_buffer_rsrc_t symp = symbol_buffer(hp, tabs_ok ? tpi : 0), symq = symbol_buffer(hs, tabs_ok ? tqi : 0);
+    Stage<KSP / C3_DEC_NT> sp_;
+    Stage<KSQ / C3_DEC_NT> sq_;
+    sp_.load(symp, 0);
+    sq_.load(symq, 0);
+    uint32_t start_p = 0, start_q = 0;
+    int32_t xp = 0, xq = 0;
+    if (active) {
+        start_p = hp.chunk_bit[cp0 + c];
+        start_q = hs.chunk_bit[cq0 + c];
+        xp = hp.chunk_prev[cp0 + c];
+        xq = hs.chunk_prev[cq0 + c];
+    }
+    // stage the words when both streams' spans fit and the index is in order
+    Span sp{0, 0}, sq{0, 0};
+    bool fits = false;
+    if (nact > 0) {
+        const uint32_t fp = hp.chunk_bit[cp0 + task.chunk0], lp = hp.chunk_bit[cp0 + task.chunk0 + nact - 1];
+        const uint32_t fq = hs.chunk_bit[cq0 + task.chunk0], lq = hs.chunk_bit[cq0 + task.chunk0 + nact - 1];
+        sp = span_of(fp, lp);
+        sq = span_of(fq, lq);
+        fits = sp.n <= kPairWords && sq.n <= kPairWords && sp.n + sq.n <= kPairWords;
+        fits = !__syncthreads_or(!fits || (active && (start_p < fp || start_p > lp || start_q < fq || start_q > lq)));
+    }
+    {
+        Stage<16> wq_, wp_;
+        if (fits) {
+            wp_.load(rsp, sp.w0);
+            wq_.load(rsq, sq.w0);
+        }
+        stage_table(SP, tabs + (tabs_ok ? tpi : 0));
+        stage_table(SQ, tabs + hp.ntable + (tabs_ok ? tqi : 0));
+        sp_.symbols(SP);
+        sq_.symbols(SQ);
+        if (fits) {
+            wp_.words(W, sp.n);
+            wq_.words(W + sp.n, sq.n);
+            stage_rest(W, rsp, sp.w0, sp.n);
+            stage_rest(W + sp.n, rsq, sq.w0, sq.n);
+        }
+    }
+    __syncthreads();
+    const bool codes_ok = tabs_ok && SP.T.ok && SQ.T.ok && SQ.T.nsym < 65535;
+    uint32_t bad = codes_ok ? 0u : C3_ERR_CODE;
+    if (l < task.nchunk && c >= nch_idx) bad |= C3_ERR_CHUNK;
+    if (!words_ok) bad |= C3_ERR_CHUNK;
+    // every chunk of the wave is there and whole
+    const bool full_wave = __ballot(active && (c + 1) * C <= n) == ~0ull;
+    if (active && codes_ok && words_ok) {
+        const int ns = min(C, n - c * C);
+        int32_t bitp = 0, bitq = 0;  // bits consumed by this chunk's codes
+        int32_t *po = pix_out + s0 + (int64_t)c * C;
+        uint16_t *qo = psi_out + s0 + (int64_t)c * C;
+        // the next eight codes of both streams; FULL: all of them belong to the chunk
+        auto eight = [&](auto full, auto &P, auto &Q, int k0, int *vp, int *vq, uint32_t p0, uint32_t q0) {
+            constexpr bool FULL = decltype(full)::value;
+            uint32_t ip[8], iq[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (!FULL && k0 + k == ns) {  // the segment's last chunk may be short
+                    bitp = (int32_t)(P.pos - p0);
+                    bitq = (int32_t)(Q.pos - q0);
+                }
+                // the two streams' reads are issued together
+                if (k % 2 == 0) {
+                    P.read();
+                    Q.read();
+                }
+                const uint32_t wp = P.window(), wq = Q.window();
+                const int ep = SP.T.lut[wp >> SPLIT], eq = SQ.T.lut[wq >> SPLIT];
+                P.L = ep;
+                Q.L = eq;
+                P.inv = Q.inv = false;
+                if (!(settled(ep) && settled(eq))) {
+                    P.search(wp, ep);
+                    Q.search(wq, eq);
+                    if ((FULL || k0 + k < ns) && (P.inv || Q.inv)) bad |= C3_ERR_CODE;
+                }
+                P.consume();
+                Q.consume();
+                ip[k] = P.index(wp);
+                iq[k] = Q.index(wq);
+                vp[k] = P.value(ip[k]);
+                vq[k] = Q.value(iq[k]);
+            }
+            escapes(P, vp, ip);
+            escapes(Q, vq, iq);
+            uint32_t mp = 0, mq = 0;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const bool v = FULL || k0 + k < ns;
+                P.x += v ? vp[k] : 0;
+                Q.x += v ? vq[k] : 0;
+                vp[k] = P.x;
+                vq[k] = Q.x;
+                mp = max(mp, (uint32_t)P.x);
+                mq = max(mq, (uint32_t)Q.x);
+            }
+            if (mp >= npix || mq >= npsi) {  // out of range: reported, stored as 0
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    if ((uint32_t)vp[k] >= npix) {
+                        if (FULL || k0 + k < ns) bad |= C3_ERR_PIX;
+                        vp[k] = 0;
+                    }
+                    if ((uint32_t)vq[k] >= npsi) {
+                        if (FULL || k0 + k < ns) bad |= C3_ERR_PSI;
+                        vq[k] = 0;
+                    }
+                }
+            }
+        };
+        auto parse = [&](auto staged) {
+            constexpr bool ST = decltype(staged)::value;
+            LaneStream<KSP, ST> P{SP, W, rsp, symp, ST ? start_p - 32 * sp.w0 : start_p, xp};
+            LaneStream<KSQ, ST> Q{SQ, W + sp.n, rsq, symq, ST ? start_q - 32 * sq.w0 : start_q, xq};
+            const uint32_t p0 = P.pos, q0 = Q.pos;
+            for (int k0 = 0; k0 < ns; k0 += 8) {
+                int vp[8], vq[8];
+                eight(std::false_type{}, P, Q, k0, vp, vq, p0, q0);
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    if (k0 + k < ns) {
+                        po[k0 + k] = vp[k];
+                        qo[k0 + k] = (uint16_t)vq[k];
+                    }
+            }
+            if (ns % 8 == 0) {
+                bitp = (int32_t)(P.pos - p0);
+                bitq = (int32_t)(Q.pos - q0);
+            }
+            xp = P.x;
+            xq = Q.x;
+        };
+        if (fits && full_wave) {
+            LaneStream<KSP, true> P{SP, W, rsp, symp, start_p - 32 * sp.w0, xp};
+            LaneStream<KSQ, true> Q{SQ, W + sp.n, rsq, symq, start_q - 32 * sq.w0, xq};
+            uint32_t pv[C], qv[C / 2];
+#pragma unroll
+            for (int k0 = 0; k0 < C; k0 += 8) {
+                int vp[8], vq[8];
+                eight(std::true_type{}, P, Q, k0, vp, vq, 0, 0);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) pv[k0 + k] = (uint32_t)vp[k];
+#pragma unroll
+                for (int k = 0; k < 8; k += 2) qv[(k0 + k) / 2] = (uint32_t)vq[k] | ((uint32_t)vq[k + 1] << 16);
+            }
+            bitp = (int32_t)(P.pos - (start_p - 32 * sp.w0));
+            bitq = (int32_t)(Q.pos - (start_q - 32 * sq.w0));
+            xp = P.x;
+            xq = Q.x;
+            const int64_t o = s0 + (int64_t)(task.chunk0 + (l & ~63)) * C;  // the wave's first sample
+            store_rows<Store16>(pv, (char *)(pix_out + o), 4 * C, 0);
+            store_rows<Store16>(pv + 16, (char *)(pix_out + o), 4 * C, 64);
+            store_rows<Store16h>(qv, (char *)(psi_out + o), 2 * C, 0);
+        } else if (fits) {
+            parse(std::true_type{});
+        } else {
+            parse(std::false_type{});
+        }
+        // chunk boundary consistency with the side index: the codes of chunk c
+        // end where chunk c + 1 starts, and the running value meets its stored one
+        if (c + 1 < nch_idx) {
+            if ((int64_t)start_p + bitp != (int64_t)hp.chunk_bit[cp0 + c + 1] || xp != hp.chunk_prev[cp0 + c + 1])
+                bad |= C3_ERR_CHUNK;
+            if ((int64_t)start_q + bitq != (int64_t)hs.chunk_bit[cq0 + c + 1] || xq != hs.chunk_prev[cq0 + c + 1])
+                bad |= C3_ERR_CHUNK;
+        }
+        if (ns > 0) {
+            if ((int64_t)start_p + bitp > 32 * nwp) bad |= C3_ERR_CHUNK;
+            if ((int64_t)start_q + bitq > 32 * nwq) bad |= C3_ERR_CHUNK;
+        }
+    }
+    if (bad) atomicOr(err, bad);
+}
+
+// One integer stream per segment (the TOD or the flag words), without range
+// checks; KIND as in k_decode1.
+template <int KIND>
+__global__ __launch_bounds__(C3_DEC_NT, 6) void k_decode32_1(LayoutDev Ld, HuffDev h, const DecTab *__restrict__ tabs,
+                                                          const DecodeTask *__restrict__ tasks, double quantum,
+                                                          uint32_t flag_mask, void *__restrict__ out,
+                                                          uint8_t *__restrict__ mask_out, uint32_t *err) {
+    StreamLds<KSQ> &S = *(StreamLds<KSQ> *)c3_dec_lds;
+    uint32_t *W = (uint32_t *)(c3_dec_lds + (kOne + 15) / 16 * 16);
+    constexpr int C = 32;
+    const DecodeTask task = tasks[blockIdx.x];
+    const int seg = task.seg;
+    const int64_t s0 = Ld.seg_off[seg];
+    const int n = (int)(Ld.seg_off[seg + 1] - s0);
+    const int ti = h.seg_table[seg];
+    const bool tabs_ok = ti >= 0 && ti < h.ntable;
+    const uint32_t *blob = h.tables + h.table_off[tabs_ok ? ti : 0];
+    const int64_t c0 = h.seg_chunk_off[seg];
+    const int nch_idx = (int)(h.seg_chunk_off[seg + 1] - c0);
+    const int64_t w0 = h.seg_word_off[seg];
+    const int64_t nw = h.seg_word_off[seg + 1] - w0;
+    const bool words_ok = nw >= 0 && nw < (1ll << 29);
+    const __amdgpu_buffer_rsrc_t rs = raw_buffer(h.words + w0, words_ok ? (int32_t)(4 * nw) : 0);
+    const int l = threadIdx.x;
+    const int c = task.chunk0 + l;
+    const bool active = l < task.nchunk && c < nch_idx;
+    const int nact = min(task.nchunk, nch_idx - task.chunk0);
+    const __amdgpu_buffer_rsrc_t sym = symbol_buffer(h, tabs_ok ? ti : 0);
+    Stage<KSQ / C3_DEC_NT> s_;
+    s_.load(sym, 0);
+    uint32_t start = 0;
+    int32_t x = 0;
+    if (active) {
+        start = h.chunk_bit[c0 + c];
+        x = h.chunk_prev[c0 + c];
+    }
+    Span sp{0, 0};
+    bool fits = false;
+    if (nact > 0) {
+        const uint32_t f = h.chunk_bit[c0 + task.chunk0], la = h.chunk_bit[c0 + task.chunk0 + nact - 1];
+        sp = span_of(f, la);
+        fits = !__syncthreads_or(sp.n > kOneWords || (active && (start < f || start > la)));
+    }
+    {
+        Stage<16> w_;
+        if (fits) w_.load(rs, sp.w0);
+        stage_table(S, tabs + (tabs_ok ? ti : 0));
+        s_.symbols(S);
+        if (fits) {
+            w_.words(W, sp.n);
+            stage_rest(W, rs, sp.w0, sp.n);
+        }
+    }
+    __syncthreads();
+    const bool codes_ok = tabs_ok && S.T.ok;
+    uint32_t bad = codes_ok ? 0u : C3_ERR_CODE;
+    if (l < task.nchunk && c >= nch_idx) bad |= C3_ERR_CHUNK;
+    if (!words_ok) bad |= C3_ERR_CHUNK;
+    const bool full_wave = __ballot(active && (c + 1) * C <= n) == ~0ull;
+    if (active && codes_ok && words_ok) {
+        const int ns = min(C, n - c * C);
+        int32_t bits = 0;
+        const int64_t o0 = s0 + (int64_t)c * C;
+        auto eight = [&](auto full, auto &P, int k0, int *v, uint32_t p0) {
+            constexpr bool FULL = decltype(full)::value;
+            uint32_t ix[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                if (!FULL && k0 + k == ns) bits = (int32_t)(P.pos - p0);
+                if (k % 2 == 0) P.read();
+                const uint32_t w = P.window();
+                const int e = S.T.lut[w >> SPLIT];
+                P.L = e;
+                P.inv = false;
+                if (!settled(e)) {
+                    P.search(w, e);
+                    if ((FULL || k0 + k < ns) && P.inv) bad |= C3_ERR_CODE;
+                }
+                P.consume();
+                ix[k] = P.index(w);
+                v[k] = P.value(ix[k]);
+            }
+            escapes(P, v, ix);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                P.x += FULL || k0 + k < ns ? v[k] : 0;
+                v[k] = P.x;
+            }
+        };
+        auto parse = [&](auto staged) {
+            constexpr bool ST = decltype(staged)::value;
+            LaneStream<KSQ, ST> P{S, W, rs, sym, ST ? start - 32 * sp.w0 : start, x};
+            const uint32_t p0 = P.pos;
+            for (int k0 = 0; k0 < ns; k0 += 8) {
+                int v[8];
+                eight(std::false_type{}, P, k0, v, p0);
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int64_t o = o0 + k0 + k;
+                    if (k0 + k >= ns) continue;
+                    if constexpr (KIND == 0) {
+                        ((float *)out)[o] = (float)(quantum * (double)v[k]);
+                    } else if constexpr (KIND == 1) {
+                        ((double *)out)[o] = quantum * (double)v[k];
+                    } else {
+                        if (out) ((uint32_t *)out)[o] = (uint32_t)v[k];
+                        if (mask_out) mask_out[o] = ((uint32_t)v[k] & flag_mask) == 0u;
+                    }
+                }
+            }
+            if (ns % 8 == 0) bits = (int32_t)(P.pos - p0);
+            x = P.x;
+        };
+        if (fits && full_wave) {
+            LaneStream<KSQ, true> P{S, W, rs, sym, start - 32 * sp.w0, x};
+            const int64_t o = s0 + (int64_t)(task.chunk0 + (l & ~63)) * C;  // the wave's first sample
+            constexpr int SZ = KIND == 1 ? 8 : 4;
+            char *ow = (char *)out + o * SZ;
+            uint32_t mb[8];  // mask bytes of the chunk
+#pragma unroll
+            for (int h = 0; h < C; h += 16) {
+                uint32_t u[16 * SZ / 4];
+#pragma unroll
+                for (int k0 = 0; k0 < 16; k0 += 8) {
+                    int v[8];
+                    eight(std::true_type{}, P, h + k0, v, 0);
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) {
+                        if constexpr (KIND == 0) {
+                            u[k0 + k] = __float_as_uint((float)(quantum * (double)v[k]));
+                        } else if constexpr (KIND == 1) {
+                            const uint64_t b = (uint64_t)__double_as_longlong(quantum * (double)v[k]);
+                            u[2 * (k0 + k)] = (uint32_t)b;
+                            u[2 * (k0 + k) + 1] = (uint32_t)(b >> 32);
+                        } else {
+                            u[k0 + k] = (uint32_t)v[k];
+                            const uint32_t m = ((uint32_t)v[k] & flag_mask) == 0u ? 1u << (8 * (k & 3)) : 0u;
+                            uint32_t &w = mb[(h + k0 + k) / 4];
+                            w = k % 4 ? w | m : m;
+                        }
+                    }
+                }
+                if (KIND != 2 || out) {
+                    store_rows<Store16>(u, ow, C * SZ, (uint32_t)(h * SZ));
+                    if constexpr (KIND == 1) store_rows<Store16>(u + 16, ow, C * SZ, (uint32_t)(h * SZ) + 64);
+                }
+            }
+            if constexpr (KIND == 2) {
+                if (mask_out) {  // the lane's 32 bytes, of any alignment
+                    ((Store16b *)(mask_out + o0))[0].v = u32x4{mb[0], mb[1], mb[2], mb[3]};
+                    ((Store16b *)(mask_out + o0))[1].v = u32x4{mb[4], mb[5], mb[6], mb[7]};
+                }
+            }
+            bits = (int32_t)(P.pos - (start - 32 * sp.w0));
+            x = P.x;
+        } else if (fits) {
+            parse(std::true_type{});
+        } else {
+            parse(std::false_type{});
+        }
+        if (c + 1 < nch_idx) {
+            if ((int64_t)start + bits != (int64_t)h.chunk_bit[c0 + c + 1] || x != h.chunk_prev[c0 + c + 1])
+                bad |= C3_ERR_CHUNK;
+        }
+        if (ns > 0 && (int64_t)start + bits > 32 * nw) bad |= C3_ERR_CHUNK;
+    }
+    if (bad) atomicOr(err, bad);
+}
+
 // ------------------------------------------------------- allocation-free variant
 // Scratch of decode_pointing_noalloc: the decoding tables of both streams,
 // then the work list, in one static array per device (held until the process
@@ -535,22 +1145,52 @@ __global__ __launch_bounds__(C3_DEC_NT) void k_decode1(LayoutDev Ld, HuffDev h, 
 
 namespace c3 {
 
+namespace {
+// The LDS decoders take streams of 32-symbol chunks whose words usually fit a
+// block's LDS (512 chunks of `words` words each on average, with a twentieth
+// to spare); blocks whose words do not fit read them from memory.
+bool staged_words(int64_t words, int64_t nchunk, uint32_t room) {
+    return nchunk > 0 && (double)words / (double)nchunk * C3_DEC_NT * 1.05 + 2 * kWordsPer <= (double)room;
+}
+hipError_t dec_attributes() {
+    static const hipError_t done = [] {
+        hipError_t e = hipSuccess;
+        auto set = [&](const void *f) {
+            const hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, C3_LDS_MAX - 4096);
+            if (r != hipSuccess) e = r;
+        };
+        set((const void *)k_decode32);
+        set((const void *)k_decode32_1<0>);
+        set((const void *)k_decode32_1<1>);
+        set((const void *)k_decode32_1<2>);
+        return e;
+    }();
+    return done;
+}
+
+template <int KIND>
+void launch_decode1(hipStream_t st, const LayoutDev &L, const HuffDev &h, DecTab *tabs, const DecodeTask *tasks,
+                    int ntask, double quantum, uint32_t flag_mask, void *out, uint8_t *mask_out, uint32_t *err) {
+    const dim3 g(ntask), b(C3_DEC_NT);
+    HuffDev none = h;
+    none.ntable = 0;
+    hipLaunchKernelGGL(k_tables, dim3(h.ntable), dim3(1024), 0, st, h, none, tabs);
+    if (h.chunk_len == 32 && staged_words(h.nwords, h.nchunk, kOneWords))
+        hipLaunchKernelGGL(k_decode32_1<KIND>, g, b, kOneLds, st, L, h, tabs, tasks, quantum, flag_mask, out, mask_out,
+                           err);
+    else
+        hipLaunchKernelGGL(k_decode1<KIND>, g, b, 0, st, L, h, tabs, tasks, quantum, flag_mask, out, mask_out, err);
+}
+}  // namespace
+
 hipError_t launch_decode_stream(hipStream_t st, const LayoutDev &L, const HuffDev &h, DecTab *tabs,
                                 const DecodeTask *tasks, int ntask, int kind, double quantum,
                                 uint32_t flag_mask, void *out, uint8_t *mask_out, uint32_t *err) {
     if (ntask <= 0) return hipSuccess;
-    HuffDev none = h;
-    none.ntable = 0;
-    hipLaunchKernelGGL(k_tables, dim3(h.ntable), dim3(C3_NT), 0, st, h, none, tabs);
-    if (kind == 0)
-        hipLaunchKernelGGL(k_decode1<0>, dim3(ntask), dim3(C3_DEC_NT), 0, st, L, h, tabs, tasks, quantum, flag_mask,
-                           out, mask_out, err);
-    else if (kind == 1)
-        hipLaunchKernelGGL(k_decode1<1>, dim3(ntask), dim3(C3_DEC_NT), 0, st, L, h, tabs, tasks, quantum, flag_mask,
-                           out, mask_out, err);
-    else
-        hipLaunchKernelGGL(k_decode1<2>, dim3(ntask), dim3(C3_DEC_NT), 0, st, L, h, tabs, tasks, quantum, flag_mask,
-                           out, mask_out, err);
+    const hipError_t e = dec_attributes();
+    if (e != hipSuccess) return e;
+    auto *go = kind == 0 ? launch_decode1<0> : kind == 1 ? launch_decode1<1> : launch_decode1<2>;
+    go(st, L, h, tabs, tasks, ntask, quantum, flag_mask, out, mask_out, err);
     return hipGetLastError();
 }
 
@@ -587,9 +1227,14 @@ hipError_t launch_decode(hipStream_t st, const LayoutDev &L, const HuffDev &hp, 
                          DecTab *tabs, const DecodeTask *tasks, int ntask, int32_t *pix_out,
                          uint16_t *psi_out, uint32_t *err) {
     if (ntask <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_tables, dim3(hp.ntable + hs.ntable), dim3(C3_NT), 0, st, hp, hs, tabs);
-    hipLaunchKernelGGL(k_decode, dim3(ntask), dim3(C3_DEC_NT), 0, st, L, hp, hs, tabs, tasks, pix_out,
-                       psi_out, err);
+    const hipError_t e = dec_attributes();
+    if (e != hipSuccess) return e;
+    const dim3 g(ntask), b(C3_DEC_NT);
+    hipLaunchKernelGGL(k_tables, dim3(hp.ntable + hs.ntable), dim3(1024), 0, st, hp, hs, tabs);
+    if (hp.chunk_len == 32 && staged_words(hp.nwords + hs.nwords, hp.nchunk, kPairWords))
+        hipLaunchKernelGGL(k_decode32, g, b, kPairLds, st, L, hp, hs, tabs, tasks, pix_out, psi_out, err);
+    else
+        hipLaunchKernelGGL(k_decode, g, b, 0, st, L, hp, hs, tabs, tasks, pix_out, psi_out, err);
     return hipGetLastError();
 }
 
