@@ -89,13 +89,13 @@ struct Plan {
     // FFT batches: contiguous ranges of the column/row task lists whose
     // segments share one workspace region (sized to stay cache resident)
     struct ColGroup {
-        int m1reg;                        // register column length, 0: LDS tiles
+        int cls;                          // class of register column lengths, -1: LDS tiles
         int t0, nt;                       // range of the column task list
     };
     struct RowGroup {
         int lds;                          // dynamic LDS bytes of the launch
         int t0, nt;                       // range of the row task list
-        int rowc;                         // row length of a compiled row kernel, 0: generic
+        int rowc;                         // compiled rows: 1, 2 (wide registers); 0: generic
         bool pair_rows = false;           // rows the compiled kernel's pair tasks cover (not mode 3)
     };
     struct Batch {
@@ -431,13 +431,13 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
         return P->h_segs[a].n > P->h_segs[b].n;
     });
     // batches in LPT order; each batch reuses the workspace from offset 0.
-    // Column tasks of a batch are grouped by column kernel (one launch each).
-    // Row tasks are grouped by how many row blocks fit on a CU (their LDS is
-    // two rows of M2), each launch sized to its own longest row.
+    // Column tasks of a batch are grouped by class of column length, compiled
+    // rows by register class and blocks per CU, the others by blocks per CU
+    // (their LDS is two rows of M2): one launch each, sized to its longest row.
     const int esz = mixed ? (int)sizeof(cx<float>) : (int)sizeof(cx<double>);
     std::vector<ColTask> col;
     std::vector<RowTask> row;
-    std::map<int, std::vector<ColTask>> bcol;            // m1reg -> column tasks of the open batch
+    std::map<int, std::vector<ColTask>> bcol;            // column class -> tasks of the open batch
     std::map<int, std::pair<int, std::vector<RowTask>>> brow;  // -blocks per CU -> (lds, row tasks)
     std::map<int, std::vector<RowTask>> browc;           // compiled row length -> two-row tasks
     std::map<int, std::vector<RowTask>> bself;           // compiled row length -> rows k1 = 0, M1/2
@@ -445,8 +445,8 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
     auto close_batch = [&]() {
         cur.col0 = (int)col.size();
         for (auto &kv : bcol) {
-            // register column kernels (kv.first = M1 > 0) return on an empty task
-            if (kv.first > 0 && !kv.second.empty())
+            // register column kernels return on an empty task
+            if (kv.first >= 0 && !kv.second.empty())
                 kv.second = xcd_order(kv.second, [](const ColTask &t) { return t.seg; }, empty_col(kv.second[0]));
             cur.groups.push_back({kv.first, (int)col.size(), (int)kv.second.size()});
             col.insert(col.end(), kv.second.begin(), kv.second.end());
@@ -472,16 +472,26 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
             for (size_t i = 0; i + 1 < v.size(); i += 2) {
                 RowTask t = v[i];
                 t.pad[0] = 1 + v[i + 1].seg;
-                t.pad[1] = v[i + 1].k1;
+                t.pad[1] |= v[i + 1].k1;
                 t.off_b = v[i + 1].off_a;
                 browc[kv.first].push_back(t);
             }
             singles.insert(singles.end(), v.begin(), v.end());
         }
-        for (auto &kv : browc) {
-            kv.second = xcd_order(kv.second, row_seg, empty_row());
-            cur.rgroups.push_back({2 * kv.first * esz, (int)row.size(), (int)kv.second.size(), kv.first});
-            row.insert(row.end(), kv.second.begin(), kv.second.end());
+        // one launch per register class and blocks per CU (a launch's LDS is its
+        // longest row's), longest rows first
+        std::map<std::pair<int, int>, std::pair<int, std::vector<RowTask>>> launches;
+        for (auto it = browc.rbegin(); it != browc.rend(); ++it) {
+            const int rl = 2 * it->first * esz;
+            auto &g = launches[{c3rowc::wide(it->first) ? 2 : 1, std::min(3, C3_LDS_MAX / rl)}];
+            g.first = std::max(g.first, rl);
+            g.second.insert(g.second.end(), it->second.begin(), it->second.end());
+        }
+        for (auto &kv : launches) {
+            std::vector<RowTask> &v = kv.second.second;
+            v = xcd_order(v, row_seg, empty_row());
+            cur.rgroups.push_back({kv.second.first, (int)row.size(), (int)v.size(), kv.first.first});
+            row.insert(row.end(), v.begin(), v.end());
         }
         for (auto &kv : brow) {
             kv.second.second = xcd_order(kv.second.second, row_seg, empty_row());
@@ -515,7 +525,7 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
         g.scr_off = scr;
         scr += fp.M;
         P->work_elems = std::max(P->work_elems, scr);
-        std::vector<ColTask> &cv = bcol[fp.colreg ? fp.M1 : 0];
+        std::vector<ColTask> &cv = bcol[fp.colreg ? c3::fft_col_class(fp.M1) : -1];
         for (int c0 = 0; c0 < fp.M2; c0 += fp.B) {
             ColTask ct;
             memset(&ct, 0, sizeof(ct));
@@ -526,6 +536,7 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
             ct.c0 = c0;
             ct.n = g.n;
             ct.M2 = fp.M2;
+            ct.pad[0] = fp.colreg ? fp.M1 : 0;
             cv.push_back(ct);
         }
         const int rl = 2 * fp.M2 * esz;
@@ -538,6 +549,7 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
             rt.off_b = g.scr_off + (int64_t)((fp.M1 - k1) % fp.M1) * fp.M2;
             rt.seg = s;
             rt.k1 = k1;
+            rt.pad[1] = fp.twr >= 0 ? fp.M2 << 16 : 0;
             // rows k1 and M1 - k1 distinct: the compiled kernel of the row length
             if (fp.twr >= 0 && k1 > 0 && 2 * k1 != fp.M1) {
                 browc[fp.M2].push_back(rt);
@@ -944,10 +956,10 @@ tod_status run_fft(tod_ctx ctx, hipStream_t st, Plan *P, int mixed, const c3::Ff
                     ag.nrow_tasks = g.nt;
                     ag.row_lds = g.lds;
                     KTimer kt(ctx, K_ROW, st);
-                    if (g.rowc && c3::rowc_supported(mixed, g.rowc, a.mode))
-                        HIPCHK(c3::launch_rowc(st, ag, g.rowc));
+                    if (g.rowc && c3::rowc_supported(mixed, a.mode))
+                        HIPCHK(c3::launch_rowc(st, ag, g.rowc == 2));
                     else
-                        HIPCHK(c3::launch_fft_pass(st, mixed, ag, pass, 0));
+                        HIPCHK(c3::launch_fft_pass(st, mixed, ag, pass));
                 }
                 continue;
             }
@@ -956,7 +968,10 @@ tod_status run_fft(tod_ctx ctx, hipStream_t st, Plan *P, int mixed, const c3::Ff
                 ag.col_tasks = (const ColTask *)P->col_tasks.p + g.t0;
                 ag.ncol_tasks = g.nt;
                 KTimer kt(ctx, K_COLF + pass, st);
-                HIPCHK(c3::launch_fft_pass(st, mixed, ag, pass, g.m1reg));
+                if (g.cls >= 0)
+                    HIPCHK(c3::launch_fft_col_reg(st, mixed, ag, pass, g.cls));
+                else
+                    HIPCHK(c3::launch_fft_pass(st, mixed, ag, pass));
             }
         }
     }

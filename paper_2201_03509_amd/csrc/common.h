@@ -96,7 +96,7 @@ struct ColTask {
     int32_t seg, c0;
     int32_t n;           // samples
     int32_t M2;          // row length of the split
-    int32_t pad[2];
+    int32_t pad[2];      // pad[0]: M1, the column length, of a register column task
 };
 
 // Row-pass work item: rows k1 and M1 - k1 of one segment's transform, with
@@ -106,7 +106,8 @@ struct RowTask {
     int64_t off_a;       // row k1
     int64_t off_b;       // row (M1 - k1) mod M1
     int32_t seg, k1;
-    int32_t pad[2];
+    int32_t pad[2];      // compiled rows: pad[1] >> 16 the row length; two rows k1 = 0 or M1/2 in
+                         // one task: pad[0] = 1 + the second row's segment, pad[1] & 0xFFFF its k1
 };
 
 // Context-side view of the layout kept on the device.
@@ -262,18 +263,18 @@ struct FftArgs {
 // pass 0: forward column FFTs; 1: row pass (mode 0 n_corr draw, 1 Whittle sums,
 // 2 Fourier-diagonal filter, 3 inverse transform of a drawn spectrum: no
 // forward transform, no input, 4 periodogram summed into log-frequency bins:
-// no inverse transform); 2: inverse column FFTs.  m1reg > 0 selects the
-// register column kernels for that column length (passes 0 and 2); 0 the LDS
-// column tiles.
-hipError_t launch_fft_pass(hipStream_t st, int prec_mixed, const FftArgs &a, int pass, int m1reg);
-// register column kernels (fftcol.hip); returns hipErrorInvalidValue for a
-// column length without a compiled kernel
-hipError_t launch_fft_col_reg(hipStream_t st, int prec_mixed, const FftArgs &a, int pass, int m1);
+// no inverse transform); 2: inverse column FFTs.  Column passes: LDS tiles.
+hipError_t launch_fft_pass(hipStream_t st, int prec_mixed, const FftArgs &a, int pass);
+// register column kernels (fftcol.hip) for the tasks of one class of column
+// lengths (fft_col_class)
+hipError_t launch_fft_col_reg(hipStream_t st, int prec_mixed, const FftArgs &a, int pass, int cls);
 bool fft_col_reg_supported(int prec_mixed, int m1);
-// row kernels compiled per row length (rowc.hip): FP32, modes 0, 1, 2 and 4, the
-// two-row tasks (0 < k1 < M1/2) of plans whose M2 is compiled
-bool rowc_supported(int prec_mixed, int L, int mode);
-hipError_t launch_rowc(hipStream_t st, const FftArgs &a, int L);
+int fft_col_class(int m1);
+// rows compiled per row length (rowc.hip): FP32, modes 0, 1, 2 and 4, the
+// two-row tasks of plans whose M2 is compiled, of one register class
+// (c3rowc::wide); a.row_lds: the longest row's
+bool rowc_supported(int prec_mixed, int mode);
+hipError_t launch_rowc(hipStream_t st, const FftArgs &a, bool wide);
 hipError_t rowc_init_attributes();
 // raise the dynamic LDS limit of the FFT kernels (once per process)
 hipError_t fft_init_attributes();

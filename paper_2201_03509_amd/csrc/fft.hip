@@ -580,10 +580,9 @@ hipError_t fft_init_attributes() {
     return e;
 }
 
-hipError_t launch_fft_pass(hipStream_t st, int mixed, const FftArgs &a, int pass, int m1reg) {
+hipError_t launch_fft_pass(hipStream_t st, int mixed, const FftArgs &a, int pass) {
     if (pass == 1 && a.nrow_tasks <= 0) return hipSuccess;
     if (pass != 1 && a.ncol_tasks <= 0) return hipSuccess;
-    if (pass != 1 && m1reg > 0) return launch_fft_col_reg(st, mixed, a, pass, m1reg);
     const unsigned lc = (unsigned)a.col_lds, lr = (unsigned)a.row_lds;
     if ((pass == 1 ? lr : lc) > 65536u) {
         hipError_t e = fft_init_attributes();

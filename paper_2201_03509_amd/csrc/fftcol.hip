@@ -67,19 +67,18 @@ __device__ __forceinline__ void col_twiddles(const cx<float> *pool, const FftPla
 }
 
 // ------------------------------------------------------------- pass 1
-template <int M1>
-__global__ __launch_bounds__(C3_COL_NT) void k_colr_fwd(FftArgs a) {
+template <int M1, int IN>
+__device__ __forceinline__ void col_fwd(const FftArgs &a, const ColTask &sg) {
     // the column's loads need only the task: they are issued first, and the
     // segment's plan (twiddles) loads while they are in flight.  In the
     // masked draw a converged segment's block returns before any load.
-    const ColTask sg = a.col_tasks[blockIdx.x];
     const int M2 = sg.M2;
     const int j2 = sg.c0 + (int)threadIdx.x;
     if (j2 >= M2) return;
     if (a.active && !a.active[sg.seg]) return;  // converged segment (whole block)
     const uint32_t n = (uint32_t)sg.n, n2 = 2u * (uint32_t)sg.n;
     cx<float> x[M1];
-    if (a.full_io) {
+    if constexpr (IN == 0) {
         // a whole extended vector (N reals = M complex at the segment's offset)
         const cx<float> *v = (const cx<float> *)a.in_a + sg.ext_off;
         const uint32_t lo = 8u * (uint32_t)j2;
@@ -88,7 +87,7 @@ __global__ __launch_bounds__(C3_COL_NT) void k_colr_fwd(FftArgs a) {
             x[j1] = ld_off<cx<float>>(v + (int64_t)j1 * M2, lo);
             if ((j1 & 15) == 15) __builtin_amdgcn_sched_barrier(0);
         }
-    } else if (!a.in_b && !a.in_a_f64) {
+    } else if constexpr (IN == 1) {
         // r = in_a (FP32): the sweep's residual (n > 12 here: M >= M1 >= 16
         // is the next 5-smooth length >= n)
         const __amdgpu_buffer_rsrc_t r =
@@ -100,7 +99,7 @@ __global__ __launch_bounds__(C3_COL_NT) void k_colr_fwd(FftArgs a) {
             // load: 16 rows in flight is plenty
             if ((j1 & 15) == 15) __builtin_amdgcn_sched_barrier(0);
         }
-    } else if (a.in_b && !a.in_a_f64 && !a.in_b_f64) {
+    } else if constexpr (IN == 2) {
         // r = in_a - in_b, both FP32 (d and s of a standalone draw): every
         // load of the column is issued before the first subtraction
         const __amdgpu_buffer_rsrc_t ra =
@@ -137,15 +136,17 @@ __global__ __launch_bounds__(C3_COL_NT) void k_colr_fwd(FftArgs a) {
     __builtin_amdgcn_sched_barrier(0);
     cx<float> *Y = (cx<float> *)a.work + sg.scr_off;
     const uint32_t lo = 8u * (uint32_t)j2;
+    // which of a product's two terms is rounded before their sum is written out:
+    // left to the compiler it varies with the kernel around it
     col_twiddles<M1, tw_split(M1)>((const cx<float> *)a.twpool, p, j2, [&](int k1, cx<float> w) {
-        st_off(Y + (int64_t)k1 * M2, lo, cmul(x[k1], w));
+        const cx<float> v = x[k1];
+        st_off(Y + (int64_t)k1 * M2, lo, cx<float>{fmaf(v.x, w.x, -(v.y * w.y)), fmaf(v.x, w.y, v.y * w.x)});
     });
 }
 
 // ------------------------------------------------------------- pass 3
 template <int M1>
-__global__ __launch_bounds__(C3_COL_NT) void k_colr_inv(FftArgs a) {
-    const ColTask sg = a.col_tasks[blockIdx.x];
+__device__ __forceinline__ void col_inv(const FftArgs &a, const ColTask &sg) {
     const int M2 = sg.M2;
     const int j2 = sg.c0 + (int)threadIdx.x;
     if (j2 >= M2) return;
@@ -157,7 +158,9 @@ __global__ __launch_bounds__(C3_COL_NT) void k_colr_inv(FftArgs a) {
     for (int k1 = 0; k1 < M1; ++k1) x[k1] = ld_off<cx<float>>(Y + (int64_t)k1 * M2, lo);
     const FftPlan &p = a.plans[a.segs[sg.seg].plan];
     col_twiddles<M1, tw_split(M1)>((const cx<float> *)a.twpool, p, j2, [&](int k1, cx<float> w) {
-        x[k1] = cmulc(x[k1], w);  // times w_M^(-j2 k1)
+        // times w_M^(-j2 k1), rounded as written (see the forward pass)
+        const cx<float> v = x[k1];
+        x[k1] = cx<float>{fmaf(v.x, w.x, v.y * w.y), fmaf(v.y, w.x, -(v.x * w.y))};
     });
     reg_fft<M1, 1>(x);
     if (a.full_io) {
@@ -180,6 +183,30 @@ __global__ __launch_bounds__(C3_COL_NT) void k_colr_inv(FftArgs a) {
     }
 }
 
+// Every column length of a register class in one kernel (one launch instead of
+// one per length, as in the row pass); the block's length is in its task.
+constexpr int col_class(int M1) { return M1 <= 36 ? 0 : M1 <= 64 ? 1 : 2; }
+constexpr int col_waves(int cls) { return cls == 0 ? 4 : cls == 1 ? 3 : 2; }  // per SIMD
+
+// PASS 0 reads its input as IN says (col_input), PASS 2 ignores it.
+template <int CLS, int PASS, int IN>
+__global__ __launch_bounds__(C3_COL_NT, col_waves(CLS)) void k_colr(FftArgs a) {
+    const ColTask sg = a.col_tasks[blockIdx.x];
+    switch (sg.pad[0]) {
+#define C3_COL_CASE(M)                           \
+    case M:                                      \
+        if constexpr (col_class(M) == CLS) {     \
+            if constexpr (PASS == 0)             \
+                col_fwd<M, IN>(a, sg);           \
+            else                                 \
+                col_inv<M>(a, sg);               \
+        }                                        \
+        break;
+        C3_COLREG_LIST(C3_COL_CASE)
+#undef C3_COL_CASE
+    }
+}
+
 }  // namespace
 
 namespace c3 {
@@ -196,23 +223,34 @@ bool fft_col_reg_supported(int mixed, int m1) {
     }
 }
 
-hipError_t launch_fft_col_reg(hipStream_t st, int mixed, const FftArgs &a, int pass, int m1) {
+int fft_col_class(int m1) { return col_class(m1); }
+
+hipError_t launch_fft_col_reg(hipStream_t st, int mixed, const FftArgs &a, int pass, int cls) {
     if (!mixed || (pass != 0 && pass != 2)) return hipErrorInvalidValue;
     if (a.ncol_tasks <= 0) return hipSuccess;
     const dim3 g(a.ncol_tasks), b(C3_COL_NT);
-    switch (m1) {
-#define C3_CASE(M)                                                     \
-    case M:                                                            \
-        if (pass == 0)                                                 \
-            hipLaunchKernelGGL(k_colr_fwd<M>, g, b, 0, st, a);         \
-        else                                                           \
-            hipLaunchKernelGGL(k_colr_inv<M>, g, b, 0, st, a);         \
+    const int in = a.full_io ? 0 : a.in_a_f64 || (a.in_b && a.in_b_f64) ? 3 : a.in_b ? 2 : 1;
+#define C3_COL_LAUNCH(CLS)                                              \
+    case CLS:                                                           \
+        if (pass == 2)                                                  \
+            hipLaunchKernelGGL((k_colr<CLS, 2, 0>), g, b, 0, st, a);    \
+        else if (in == 0)                                               \
+            hipLaunchKernelGGL((k_colr<CLS, 0, 0>), g, b, 0, st, a);    \
+        else if (in == 1)                                               \
+            hipLaunchKernelGGL((k_colr<CLS, 0, 1>), g, b, 0, st, a);    \
+        else if (in == 2)                                               \
+            hipLaunchKernelGGL((k_colr<CLS, 0, 2>), g, b, 0, st, a);    \
+        else                                                            \
+            hipLaunchKernelGGL((k_colr<CLS, 0, 3>), g, b, 0, st, a);    \
         break;
-        C3_COLREG_LIST(C3_CASE)
-#undef C3_CASE
+    switch (cls) {
+        C3_COL_LAUNCH(0)
+        C3_COL_LAUNCH(1)
+        C3_COL_LAUNCH(2)
     default:
         return hipErrorInvalidValue;
     }
+#undef C3_COL_LAUNCH
     return hipGetLastError();
 }
 

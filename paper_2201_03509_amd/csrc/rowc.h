@@ -76,6 +76,18 @@ constexpr long stage_off(int L, int s) {
 }
 constexpr long table_size(int L) { return stage_off(L, 3); }
 
+// lengths whose butterflies need more than 80 registers a thread (four waves per
+// SIMD; the others run six)
+constexpr bool wide(int L) {
+    switch (L) {
+    case 2500: case 3125: case 3240: case 3456: case 3888: case 4050: case 4320: case 4500: case 4608: case 4800:
+    case 4860:
+        return true;
+    default:
+        return false;
+    }
+}
+
 inline bool compiled(int L) {
     switch (L) {
 #define C3_ROWC_CASE(LL) case LL:

@@ -410,14 +410,13 @@ __device__ __forceinline__ void whittle_flush(const FftArgs &a, double *red, Wsu
 }
 
 template <int L, int MODE>
-__global__ __launch_bounds__(NT) void k_rowc(FftArgs a) {
+__device__ __forceinline__ void row_body(const FftArgs &a, const RowTask &task, double *hist) {
     static_assert(plan(L).r[0] > 0, "row length without a three-stage plan");
     cx<float> *buf = (cx<float> *)c3_rowc_lds;  // 2 L elements
-    const RowTask task = a.row_tasks[blockIdx.x];
-    if (task.seg < 0) return;                      // an empty task (launch padding)
     // a task of two rows that each hold their own mirror modes (k1 = 0 or
-    // M1/2): pad[0] = 1 + the second row's segment, pad[1] = its k1
+    // M1/2): pad[0] = 1 + the second row's segment, kb = its k1
     const bool self = task.pad[0] > 0;
+    const int kb = task.pad[1] & 0xFFFF;
     // converged segments (masked draw): no load.  A task of two segments runs
     // while either is active; the workspace rows of a converged one are not
     // read again (its column passes return before any load or store).
@@ -438,14 +437,13 @@ __global__ __launch_bounds__(NT) void k_rowc(FftArgs a) {
     rstage<L, 2, -1, 0>(buf, nullptr, nullptr, nullptr, nullptr, tws);
 
     if constexpr (MODE == 4) {
-        __shared__ double hist[C3_XI_NBIN];
         for (int i = threadIdx.x; i < C3_XI_NBIN; i += NT) hist[i] = 0.0;
         __syncthreads();
         if (self) {
             const int seg1 = task.pad[0] - 1;
             self_row_periodogram<L>(a, buf, seg, ka, 0, twh, hist);
             hist_flush(a, hist, seg);
-            self_row_periodogram<L>(a, buf, seg1, task.pad[1], 1, twh, hist);
+            self_row_periodogram<L>(a, buf, seg1, kb, 1, twh, hist);
             hist_flush(a, hist, seg1);
         } else {
             pair_row_periodogram<L>(a, buf, seg, sg, p, ka, twh, hist);
@@ -458,7 +456,7 @@ __global__ __launch_bounds__(NT) void k_rowc(FftArgs a) {
         if (self) {
             const int seg1 = task.pad[0] - 1;
             const Wsum w0 = self_row_whittle<L>(a, buf, seg, ka, 0, twh);
-            const Wsum w1 = self_row_whittle<L>(a, buf, seg1, task.pad[1], 1, twh);
+            const Wsum w1 = self_row_whittle<L>(a, buf, seg1, kb, 1, twh);
             __syncthreads();
             whittle_flush(a, red, w0, seg);
             whittle_flush(a, red, w1, seg1);
@@ -471,7 +469,7 @@ __global__ __launch_bounds__(NT) void k_rowc(FftArgs a) {
         if (self) {
             // the stage and w_2L tables depend on L alone: the first row's serve both
             self_row_modes<L, MODE>(a, buf, seg, ka, 0, twh);
-            self_row_modes<L, MODE>(a, buf, task.pad[0] - 1, task.pad[1], 1, twh);
+            self_row_modes<L, MODE>(a, buf, task.pad[0] - 1, kb, 1, twh);
         } else {
             pair_row_modes<L, MODE>(a, buf, seg, sg, p, ka, twh);
         }
@@ -483,12 +481,37 @@ __global__ __launch_bounds__(NT) void k_rowc(FftArgs a) {
     }
 }
 
+// Every row length of a register class in one kernel: a set whose segments
+// have several lengths would otherwise run its rows as that many launches one
+// after the other, each with its own tail and, for few segments, on a part of
+// the chip.  The block's length is in its task, so the choice is uniform.  The
+// classes keep a short length's occupancy from falling to that of the lengths
+// whose butterflies take twice the registers.
+template <int MODE, bool WIDE>
+__global__ __launch_bounds__(NT, WIDE ? 4 : 6) void k_rowc(FftArgs a) {
+    const RowTask task = a.row_tasks[blockIdx.x];
+    if (task.seg < 0) return;  // an empty task (launch padding)
+    double *hist = nullptr;    // mode 4: the block's periodogram bins
+    if constexpr (MODE == 4) {
+        __shared__ double bins[C3_XI_NBIN];
+        hist = bins;
+    }
+    switch (task.pad[1] >> 16) {
+#define C3_ROWC_CASE(LL)                                                        \
+    case LL:                                                                    \
+        if constexpr (c3rowc::wide(LL) == WIDE) row_body<LL, MODE>(a, task, hist); \
+        break;
+        C3_ROWC_LIST(C3_ROWC_CASE)
+#undef C3_ROWC_CASE
+    }
+}
+
 }  // namespace
 
 namespace c3 {
 
-bool rowc_supported(int mixed, int L, int mode) {
-    return mixed && (mode == 0 || mode == 1 || mode == 2 || mode == 4) && c3rowc::compiled(L);
+bool rowc_supported(int mixed, int mode) {
+    return mixed && (mode == 0 || mode == 1 || mode == 2 || mode == 4);
 }
 
 hipError_t rowc_init_attributes() {
@@ -497,39 +520,37 @@ hipError_t rowc_init_attributes() {
         hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, C3_LDS_MAX - 4096);
         if (r != hipSuccess) e = r;
     };
-#define C3_ROWC_ATTR(LL)                       \
-    set((const void *)k_rowc<LL, 0>);          \
-    set((const void *)k_rowc<LL, 1>);          \
-    set((const void *)k_rowc<LL, 2>);          \
-    set((const void *)k_rowc<LL, 4>);
-    C3_ROWC_LIST(C3_ROWC_ATTR)
-#undef C3_ROWC_ATTR
+    set((const void *)k_rowc<0, false>);
+    set((const void *)k_rowc<1, false>);
+    set((const void *)k_rowc<2, false>);
+    set((const void *)k_rowc<4, false>);
+    set((const void *)k_rowc<0, true>);
+    set((const void *)k_rowc<1, true>);
+    set((const void *)k_rowc<2, true>);
+    set((const void *)k_rowc<4, true>);
     return e;
 }
 
-hipError_t launch_rowc(hipStream_t st, const FftArgs &a, int L) {
+hipError_t launch_rowc(hipStream_t st, const FftArgs &a, bool wide) {
     if (a.nrow_tasks <= 0) return hipSuccess;
     const dim3 g(a.nrow_tasks), b(NT);
-    const unsigned lds = 2u * (unsigned)L * (unsigned)sizeof(cx<float>);
-    switch (L) {
-#define C3_ROWC_LAUNCH(LL)                                                    \
-    case LL:                                                                  \
-        if (a.mode == 0)                                                      \
-            hipLaunchKernelGGL((k_rowc<LL, 0>), g, b, lds, st, a);            \
-        else if (a.mode == 1)                                                 \
-            hipLaunchKernelGGL((k_rowc<LL, 1>), g, b, lds, st, a);            \
-        else if (a.mode == 2)                                                 \
-            hipLaunchKernelGGL((k_rowc<LL, 2>), g, b, lds, st, a);            \
-        else if (a.mode == 4)                                                 \
-            hipLaunchKernelGGL((k_rowc<LL, 4>), g, b, lds, st, a);            \
-        else                                                                  \
-            return hipErrorInvalidValue;                                      \
+    const unsigned lds = (unsigned)a.row_lds;
+#define C3_ROWC_LAUNCH(MODE)                                                \
+    case MODE:                                                              \
+        if (wide)                                                           \
+            hipLaunchKernelGGL((k_rowc<MODE, true>), g, b, lds, st, a);     \
+        else                                                                \
+            hipLaunchKernelGGL((k_rowc<MODE, false>), g, b, lds, st, a);    \
         break;
-        C3_ROWC_LIST(C3_ROWC_LAUNCH)
-#undef C3_ROWC_LAUNCH
+    switch (a.mode) {
+        C3_ROWC_LAUNCH(0)
+        C3_ROWC_LAUNCH(1)
+        C3_ROWC_LAUNCH(2)
+        C3_ROWC_LAUNCH(4)
     default:
         return hipErrorInvalidValue;
     }
+#undef C3_ROWC_LAUNCH
     return hipGetLastError();
 }
 
