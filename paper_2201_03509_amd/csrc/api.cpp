@@ -19,6 +19,7 @@
 #include <vector>
 
 #include "common.h"
+#include "fp64fn.h"
 #include "rowc.h"
 #include "tune.h"
 #include "validate.h"
@@ -95,7 +96,7 @@ struct Plan {
     struct RowGroup {
         int lds;                          // dynamic LDS bytes of the launch
         int t0, nt;                       // range of the row task list
-        int rowc;                         // compiled rows: 1, 2 (wide registers); 0: generic
+        int rowc;                         // compiled rows: 1, 2 (wide registers), 3, 4 (FP64, short); 0: generic
         bool pair_rows = false;           // rows the compiled kernel's pair tasks cover (not mode 3)
     };
     struct Batch {
@@ -261,10 +262,13 @@ struct Pool {
         sub_tab[L] = off;
         return off;
     }
+    void put(long double x, long double y) {
+        re.push_back(x);
+        im.push_back(y);
+    }
     void push(int64_t m, int64_t L) {  // e^{-2 pi i m / L}
         const long double a = -2.0L * 3.14159265358979323846264338327950288L * (long double)m / (long double)L;
-        re.push_back(cosl(a));
-        im.push_back(sinl(a));
+        put(cosl(a), sinl(a));
     }
 };
 
@@ -363,6 +367,7 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
     const int nseg = L->nseg;
     P->h_segs.resize(nseg);
     Pool pool;
+    if (!mixed) c3d::table([&](long double x, long double y) { pool.put(x, y); });  // at offset 0
     int64_t scr = 0, ext = 0;
     for (int s = 0; s < nseg; ++s) {
         SegInfo &g = P->h_segs[s];
@@ -404,13 +409,13 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
             fp.twhi = (int64_t)pool.re.size();
             for (int64_t h = 0; h <= N / 1024 + 1; ++h) pool.push(h * 1024, N);
             fp.twr = fp.twh = -1;
-            if (mixed && c3rowc::compiled(ch.M2)) {
+            if (c3rowc::compiled(ch.M2, !mixed)) {
                 // the compiled row kernel's stage twiddles (rowc.h layout) and w_2L^j
                 const int L = ch.M2;
-                const c3rowc::Plan3 rp = c3rowc::plan(L);
+                const c3rowc::Plan rp = c3rowc::plan(L, !mixed);
                 fp.twr = (int64_t)pool.re.size();
-                for (int st = 1; st < 3; ++st) {
-                    const int R = rp.r[st], NS = c3rowc::row_ns(L, st);
+                for (int st = 1; st < c3rowc::stages(L, !mixed); ++st) {
+                    const int R = rp.r[st], NS = c3rowc::row_ns(L, st, !mixed);
                     for (int k = 0; k < NS; ++k)
                         for (int t = 1; t < R; ++t) pool.push((int64_t)t * k, (int64_t)NS * R);
                 }
@@ -458,10 +463,14 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
         // (pad[0] = 1 + the second row's segment, pad[1] = its k1); mode 3,
         // which has no compiled kernel, takes them one per task on the
         // generic kernel (which skips the pair tasks).  An odd one out takes
-        // the generic kernel in every mode.
+        // the generic kernel in every mode in FP32 (a launch of one block: 20
+        // us), where outputs in FP64 depend on the kernel's rounding of FP32
+        // values; in FP64 it is paired with itself.
         std::vector<RowTask> singles;
         for (auto &kv : bself) {
             std::vector<RowTask> &v = kv.second;
+            const bool twin = !mixed && v.size() % 2;
+            if (twin) v.push_back(v.back());
             if (v.size() % 2) {
                 const int rl = 2 * kv.first * esz;
                 auto &rg = brow[-std::max(1, (C3_LDS_MAX - 1024) / rl)];
@@ -476,14 +485,17 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
                 t.off_b = v[i + 1].off_a;
                 browc[kv.first].push_back(t);
             }
-            singles.insert(singles.end(), v.begin(), v.end());
+            singles.insert(singles.end(), v.begin(), v.end() - (twin ? 1 : 0));
         }
         // one launch per register class and blocks per CU (a launch's LDS is its
         // longest row's), longest rows first
         std::map<std::pair<int, int>, std::pair<int, std::vector<RowTask>>> launches;
         for (auto it = browc.rbegin(); it != browc.rend(); ++it) {
-            const int rl = 2 * it->first * esz;
-            auto &g = launches[{c3rowc::wide(it->first) ? 2 : 1, std::min(3, C3_LDS_MAX / rl)}];
+            // FP64: the mode tables behind the rows, and always two blocks (of short
+            // rows, four) to a CU
+            const int rl = 2 * it->first * esz + (mixed ? 0 : c3d::kTab * esz);
+            const int cls = !mixed ? (c3rowc::short_row(it->first) ? 4 : 3) : c3rowc::wide(it->first) ? 2 : 1;
+            auto &g = launches[{cls, std::min(mixed ? 3 : 2, C3_LDS_MAX / rl)}];
             g.first = std::max(g.first, rl);
             g.second.insert(g.second.end(), it->second.begin(), it->second.end());
         }
@@ -525,7 +537,7 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
         g.scr_off = scr;
         scr += fp.M;
         P->work_elems = std::max(P->work_elems, scr);
-        std::vector<ColTask> &cv = bcol[fp.colreg ? c3::fft_col_class(fp.M1) : -1];
+        std::vector<ColTask> &cv = bcol[fp.colreg ? c3::fft_col_class(mixed, fp.M1) : -1];
         for (int c0 = 0; c0 < fp.M2; c0 += fp.B) {
             ColTask ct;
             memset(&ct, 0, sizeof(ct));
@@ -956,8 +968,10 @@ tod_status run_fft(tod_ctx ctx, hipStream_t st, Plan *P, int mixed, const c3::Ff
                     ag.nrow_tasks = g.nt;
                     ag.row_lds = g.lds;
                     KTimer kt(ctx, K_ROW, st);
-                    if (g.rowc && c3::rowc_supported(mixed, a.mode))
-                        HIPCHK(c3::launch_rowc(st, ag, g.rowc == 2));
+                    if (g.rowc && c3::rowc_supported(a.mode))
+                        HIPCHK(g.rowc == 4   ? c3::launch_rows(st, ag)
+                               : g.rowc == 3 ? c3::launch_rowd(st, ag)
+                                             : c3::launch_rowc(st, ag, g.rowc == 2));
                     else
                         HIPCHK(c3::launch_fft_pass(st, mixed, ag, pass));
                 }

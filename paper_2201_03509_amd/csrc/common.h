@@ -9,6 +9,8 @@
 #define C3_DEC_NT 512        // threads per block of the decoders: one side-index chunk each
 #define C3_ROW_NT_F32 512    // threads per block of the FFT row pass (two blocks per CU)
 #define C3_ROW_NT_F64 1024
+#define C3_ROWC_NT 512       // threads per block of the row pass compiled per length
+#define C3_ROWS_NT 256       // the same for its short rows (FP64)
 #define C3_COL_NT 64         // threads (= columns) per block of the register column passes
 #define C3_LDS_MAX 163840    // LDS bytes one workgroup may hold on gfx950
 
@@ -17,10 +19,11 @@
 #define C3_ROW_RADICES_F32(X) X(2) X(3) X(4) X(5) X(6) X(8) X(9) X(10) X(12) X(20) X(24) X(25) X(27)
 #define C3_ROW_RADICES_F64(X) X(2) X(3) X(4) X(5) X(6) X(8) X(9) X(10)
 
-// column lengths M1 with register column kernels (5-smooth, 16..100; FP32 only)
-#define C3_COLREG_LIST(X) \
-    X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(50) X(54) X(60) X(64) X(72) X(75) X(80) X(81) \
-        X(90) X(96) X(100)
+// column lengths M1 with register column kernels (5-smooth, 16..100; in FP64 to
+// 81, 324 registers of column data)
+#define C3_COLREG_LIST_F64(X) \
+    X(16) X(18) X(20) X(24) X(25) X(27) X(30) X(32) X(36) X(40) X(45) X(48) X(50) X(54) X(60) X(64) X(72) X(75) X(80) X(81)
+#define C3_COLREG_LIST(X) C3_COLREG_LIST_F64(X) X(90) X(96) X(100)
 
 // sticky device error bits
 #define C3_ERR_CODE 1u       // bit pattern matches no code
@@ -268,14 +271,18 @@ hipError_t launch_fft_pass(hipStream_t st, int prec_mixed, const FftArgs &a, int
 // register column kernels (fftcol.hip) for the tasks of one class of column
 // lengths (fft_col_class)
 hipError_t launch_fft_col_reg(hipStream_t st, int prec_mixed, const FftArgs &a, int pass, int cls);
-bool fft_col_reg_supported(int prec_mixed, int m1);
-int fft_col_class(int m1);
-// rows compiled per row length (rowc.hip): FP32, modes 0, 1, 2 and 4, the
-// two-row tasks of plans whose M2 is compiled, of one register class
-// (c3rowc::wide); a.row_lds: the longest row's
-bool rowc_supported(int prec_mixed, int mode);
+hipError_t launch_fft_col_reg_f64(hipStream_t st, const FftArgs &a, int pass);
+int fft_col_class(int prec_mixed, int m1);
+// rows compiled per row length (rowc.hip FP32, rowd.hip FP64, rows.hip FP64 short): modes 0, 1, 2
+// and 4, the two-row tasks of plans whose M2 is compiled, in FP32 of one
+// register class (c3rowc::wide); a.row_lds: the longest row's
+bool rowc_supported(int mode);
 hipError_t launch_rowc(hipStream_t st, const FftArgs &a, bool wide);
+hipError_t launch_rowd(hipStream_t st, const FftArgs &a);
+hipError_t launch_rows(hipStream_t st, const FftArgs &a);
 hipError_t rowc_init_attributes();
+hipError_t rowd_init_attributes();
+hipError_t rows_init_attributes();
 // raise the dynamic LDS limit of the FFT kernels (once per process)
 hipError_t fft_init_attributes();
 

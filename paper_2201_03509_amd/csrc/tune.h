@@ -37,15 +37,15 @@ inline int row_cap(int mixed) { return mixed ? 5040 : 2520; }
 inline int col_tile(int mixed) { return mixed ? 4096 : 2048; }
 
 inline bool colreg_ok(int mixed, int64_t m1) {
-    if (!mixed) return false;
-    switch (m1) {
+    if (!mixed && m1 > 81) return false;  // C3_COLREG_LIST_F64
 #define C3_TUNE_OK(M) case M:
+    switch (m1) {
         C3_COLREG_LIST(C3_TUNE_OK)
         return true;
-#undef C3_TUNE_OK
     default:
         return false;
     }
+#undef C3_TUNE_OK
 }
 
 inline std::vector<int> factor235(int64_t L) {
@@ -195,24 +195,36 @@ inline bool choice_ok(const FftChoice &c, int64_t M, int mixed) {
 }
 
 inline bool default_choice(int64_t M, int mixed, FftChoice &c) {
-    // register columns where a compiled M1 fits: the largest M1 up to 64
+    // register columns where a compiled M1 fits: in FP32 the largest M1 up to 64
     // (fewest row-pass stages at two waves per SIMD in the column kernels),
-    // else the largest; otherwise LDS column tiles with the longest rows
+    // else the largest; in FP64 the smallest with a compiled row length (fewest
+    // registers a column; 1e5 samples a segment: rows and columns 650 us on the
+    // generic kernels, 285 on these; 4096 a segment, eight of them: 46 and 26);
+    // otherwise LDS column tiles with the longest rows
     const std::vector<int64_t> m1s = reg_cols(M, mixed);
+    // the last m1 <= 64 in FP32 (else the largest), the first in FP64
+    auto take = [&](int64_t m1, int64_t pick) { return pick == 0 || (mixed && m1 <= 64); };
     if (!m1s.empty()) {
-        int64_t pick = m1s.back();
-        for (int64_t m1 : m1s)
-            if (m1 <= 64) pick = m1;
+        int64_t pick = 0, pc = 0;
+        if (mixed) {
+            pick = m1s.back();
+            for (int64_t m1 : m1s)
+                if (m1 <= 64) pick = m1;
+        }
         // a row length with a compiled row kernel first (the same rule)
-        int64_t pc = 0;
         for (int64_t m1 : m1s)
-            if (c3rowc::compiled((int)(M / m1)) && (pc == 0 || m1 <= 64)) pc = m1;
+            if (c3rowc::compiled((int)(M / m1), !mixed) && take(m1, pc)) pc = m1;
         if (pc) pick = pc;
-        return make_choice(M, M / pick, mixed, 64, 0, 1, c);
+        if (pick) return make_choice(M, M / pick, mixed, 64, 0, 1, c);
     }
     const std::vector<int64_t> m2s = lds_rows(M, mixed);
     if (m2s.empty()) return false;
-    return make_choice(M, m2s.back(), mixed, 64, 0, 0, c);
+    // FP64: a row length with a compiled row kernel, the longest
+    int64_t pick = m2s.back();
+    if (!mixed)
+        for (int64_t m2 : m2s)
+            if (c3rowc::compiled((int)m2, true)) pick = m2;
+    return make_choice(M, pick, mixed, 64, 0, 0, c);
 }
 
 inline std::vector<FftChoice> candidates(int64_t M, int mixed) {
