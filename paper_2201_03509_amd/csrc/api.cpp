@@ -254,6 +254,28 @@ HuffDev make_huff_dev(const tod_huff *h) {
 struct Pool {
     std::vector<long double> re, im;
     std::map<int64_t, int64_t> sub_tab;  // L -> offset of w_L^m
+    std::map<int, std::pair<int64_t, int64_t>> row_tab;  // compiled row length -> offsets (twr, twh)
+    // the compiled row kernel's stage twiddles (rowc.h layout) and w_2L^j, once
+    // per row length; every stage's root divides 2L, so they are w_2L^j too
+    std::pair<int64_t, int64_t> add_row(int L, bool f64) {
+        auto it = row_tab.find(L);
+        if (it != row_tab.end()) return it->second;
+        const int64_t twh = (int64_t)re.size();
+        for (int j = 0; j < L; ++j) push(j, 2 * (int64_t)L);
+        const int64_t twr = (int64_t)re.size();
+        const c3rowc::Plan rp = c3rowc::plan(L, f64);
+        for (int st = 1; st < c3rowc::stages(L, f64); ++st) {
+            const int R = rp.r[st], NS = c3rowc::row_ns(L, st, f64);
+            for (int k = 0; k < NS; ++k)
+                for (int t = 1; t < R; ++t) {
+                    const int64_t j = (int64_t)t * k % ((int64_t)NS * R) * (2 * L / (NS * R));
+                    const long double sg = j < L ? 1.0L : -1.0L;
+                    const int64_t q = twh + (j < L ? j : j - L);
+                    put(sg * re[q], sg * im[q]);
+                }
+        }
+        return row_tab[L] = {twr, twh};
+    }
     int64_t add_sub(int64_t L) {
         auto it = sub_tab.find(L);
         if (it != sub_tab.end()) return it->second;
@@ -410,17 +432,9 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
             for (int64_t h = 0; h <= N / 1024 + 1; ++h) pool.push(h * 1024, N);
             fp.twr = fp.twh = -1;
             if (c3rowc::compiled(ch.M2, !mixed)) {
-                // the compiled row kernel's stage twiddles (rowc.h layout) and w_2L^j
-                const int L = ch.M2;
-                const c3rowc::Plan rp = c3rowc::plan(L, !mixed);
-                fp.twr = (int64_t)pool.re.size();
-                for (int st = 1; st < c3rowc::stages(L, !mixed); ++st) {
-                    const int R = rp.r[st], NS = c3rowc::row_ns(L, st, !mixed);
-                    for (int k = 0; k < NS; ++k)
-                        for (int t = 1; t < R; ++t) pool.push((int64_t)t * k, (int64_t)NS * R);
-                }
-                fp.twh = (int64_t)pool.re.size();
-                for (int j = 0; j < L; ++j) pool.push(j, 2 * (int64_t)L);
+                const auto t = pool.add_row(ch.M2, !mixed);
+                fp.twr = t.first;
+                fp.twh = t.second;
             }
             P->plan_of_M[M] = (int)P->h_plans.size();
             P->h_plans.push_back(fp);
