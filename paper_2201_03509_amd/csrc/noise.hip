@@ -50,16 +50,41 @@ __global__ __launch_bounds__(C3_NT) void k_xi_white(const int4 *__restrict__ til
     }
 }
 
-// wave-wide sum, every lane gets the result (fixed butterfly order)
+// v of another lane of the wave, as the DPP control CTRL says
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, true);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, true);
+    return __longlong_as_double((int64_t)((uint64_t)hi << 32 | lo));
+}
+// wave-wide sum, every lane gets the result (fixed order): between lanes 1 and 2
+// apart, the halves of 8, the halves of 16 by DPP, rows and wave halves by
+// swaps.  Six shuffles through LDS took most of a score evaluation's time.
 __device__ __forceinline__ double wsum(double v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    v += dpp<0xB1>(v);   // quad_perm [1, 0, 3, 2]
+    v += dpp<0x4E>(v);   // quad_perm [2, 3, 0, 1]
+    v += dpp<0x141>(v);  // row_half_mirror
+    v += dpp<0x140>(v);  // row_mirror
+#define C3_SWAP_SUM(SWAP)                                                                             \
+    {                                                                                                 \
+        const uint64_t b = (uint64_t)__double_as_longlong(v);                                         \
+        const auto lo = SWAP((uint32_t)b, (uint32_t)b, false, false);                                 \
+        const auto hi = SWAP((uint32_t)(b >> 32), (uint32_t)(b >> 32), false, false);                 \
+        v = __longlong_as_double((int64_t)((uint64_t)hi[0] << 32 | lo[0])) +                          \
+            __longlong_as_double((int64_t)((uint64_t)hi[1] << 32 | lo[1]));                           \
+    }
+    C3_SWAP_SUM(__builtin_amdgcn_permlane16_swap)
+    C3_SWAP_SUM(__builtin_amdgcn_permlane32_swap)
+#undef C3_SWAP_SUM
     return v;
 }
 
 #define C3_XI_PER_LANE ((C3_XI_NBIN + 63) / 64)
 
-// one wave per segment
+// one wave per segment.  Bound by its own latency: about twelve evaluations of the
+// score one after the other, and a ln Gamma per bin.  80 segments of 1e5 samples: 46
+// us with 50 evaluations, LDS shuffles and two ln Gamma a bin, 17 now.
 __global__ __launch_bounds__(C3_NT) void k_xi_sample(int nseg, const SegInfo *__restrict__ segs,
                                                      const FftPlan *__restrict__ plans,
                                                      const int32_t *__restrict__ seg_band,
@@ -108,23 +133,35 @@ __global__ __launch_bounds__(C3_NT) void k_xi_sample(int nseg, const SegInfo *__
                                              (int)(M >> ((63 - __builtin_clzll((unsigned long long)M)) - 3)) - 8);
     double Jb[C3_XI_PER_LANE], cb[C3_XI_PER_LANE], xb[C3_XI_PER_LANE], lf[C3_XI_PER_LANE];
     const double lscale = log(fs / N);
+    // first mode of bin b, at most M + 1 (the first one past the spectrum), and
+    // ln Gamma of it: bin b + 1's is the end of bin b, so one per bin does
+    int64_t first[C3_XI_PER_LANE + 1];
+    double lg[C3_XI_PER_LANE + 1];
+#pragma unroll
+    for (int j = 0; j < C3_XI_PER_LANE; ++j) {
+        const int b = lane + 64 * j;
+        const int e = (b - 7) / 8, m = (b - 7) % 8;
+        first[j] = b < 7 ? b + 1 : e < 30 ? (int64_t)(8 + m) << e : M + 1;
+        if (first[j] > M + 1) first[j] = M + 1;
+        lg[j] = 0.0;
+        if (b <= nb) lg[j] = lgamma((double)first[j]);
+    }
+    lg[C3_XI_PER_LANE] = 0.0;
+    first[C3_XI_PER_LANE] = M + 1;
+    double end_lg[C3_XI_PER_LANE];
+    int64_t end[C3_XI_PER_LANE];
+#pragma unroll
+    for (int j = 0; j < C3_XI_PER_LANE; ++j) {  // bin b + 1 is the next lane's, or lane 0's next
+        end_lg[j] = __shfl(lane == 0 ? lg[j + 1] : lg[j], (lane + 1) & 63, 64);
+        end[j] = __shfl((long long)(lane == 0 ? first[j + 1] : first[j]), (lane + 1) & 63, 64);
+    }
 #pragma unroll
     for (int j = 0; j < C3_XI_PER_LANE; ++j) {
         const int b = lane + 64 * j;
         Jb[j] = cb[j] = xb[j] = lf[j] = 0;
-        if (b >= nb) continue;
-        int64_t lo, hi;  // mode range of bin b, clipped to M
-        if (b < 7) {
-            lo = hi = b + 1;
-        } else {
-            const int e = 3 + (b - 7) / 8, m = (b - 7) % 8;
-            lo = (int64_t)(8 + m) << (e - 3);
-            hi = ((int64_t)(9 + m) << (e - 3)) - 1;
-        }
-        if (hi > M) hi = M;
-        if (lo > hi) continue;
-        const double c = (double)(hi - lo + 1);
-        const double L = lgamma((double)hi + 1.0) - lgamma((double)lo);  // sum of ln k, k = lo..hi
+        if (b >= nb || end[j] <= first[j]) continue;
+        const double c = (double)(end[j] - first[j]);
+        const double L = end_lg[j] - lg[j];  // sum of ln k over the bin
         Jb[j] = bins[(int64_t)seg * C3_XI_NBIN + b];
         cb[j] = c;
         lf[j] = lscale + L / c;                 // ln f_b
@@ -144,11 +181,10 @@ __global__ __launch_bounds__(C3_NT) void k_xi_sample(int nseg, const SegInfo *__
         if (dscore) *dscore = wsum(ds);
         return wsum(s);
     };
-    double lo = -1.0, hi = 1.0;
-    bool ok = true;
-    for (int i = 0; i < 60 && score(lo, nullptr) < 0.0; ++i) lo *= 2.0;
-    for (int i = 0; i < 60 && score(hi, nullptr) > 0.0; ++i) hi *= 2.0;
-    if (!(score(lo, nullptr) >= 0.0) || !(score(hi, nullptr) <= 0.0)) ok = false;
+    double lo = -1.0, hi = 1.0, flo = score(lo, nullptr), fhi = score(hi, nullptr);
+    for (int i = 0; i < 60 && flo < 0.0; ++i) flo = score(lo *= 2.0, nullptr);
+    for (int i = 0; i < 60 && fhi > 0.0; ++i) fhi = score(hi *= 2.0, nullptr);
+    const bool ok = flo >= 0.0 && fhi <= 0.0;
     double al = 0.5 * (lo + hi), H = 0;
     if (ok) {
         for (int i = 0; i < 200; ++i) {
@@ -156,6 +192,14 @@ __global__ __launch_bounds__(C3_NT) void k_xi_sample(int nseg, const SegInfo *__
             const double f = score(al, &ds);
             if (f > 0.0) lo = al; else hi = al;
             double nx = al - f / ds;                   // Newton step
+            // quadratic: what a step of 1e-9 leaves is below the rounding.  (Waiting
+            // for steps of 1e-15 ran into the bracket's end at the root, which the
+            // next step then left, and bisected the whole bracket again: 50
+            // evaluations of the score for 8.)
+            if (fabs(nx - al) <= 1e-9 * fmax(1.0, fabs(al))) {
+                al = nx;
+                break;
+            }
             if (!(nx > lo && nx < hi)) nx = 0.5 * (lo + hi);  // bisection fallback
             const double step = fabs(nx - al);
             al = nx;
