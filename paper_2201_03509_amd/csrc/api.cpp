@@ -166,6 +166,8 @@ struct tod_ctx_s {
     uint32_t last_err_bits = 0;
     bool timing = false;
     hipEvent_t ev[8] = {};                 // scratch events (autotuning)
+    int32_t *h_count = nullptr;            // masked draw: active segments of the last iterations (pinned)
+    hipEvent_t cg_ev[2] = {};              //   copied
     std::vector<hipEvent_t> ev_pool;       // recycled timing events
     struct Rec {
         int kid;
@@ -1044,6 +1046,12 @@ tod_status tod_ctx_create(tod_ctx *out, int device, void *hip_stream) {
         return TOD_EHIP;
     }
     for (auto &e : ctx->ev) (void)hipEventCreate(&e);
+    bool cg_ok = hipHostMalloc((void **)&ctx->h_count, 64) == hipSuccess;
+    for (auto &e : ctx->cg_ev) cg_ok = cg_ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+    if (!cg_ok) {
+        delete ctx;
+        return TOD_ENOMEM;
+    }
     if (c3::noalloc_scratch(&ctx->noalloc) != hipSuccess) {  // device is current here
         delete ctx;
         return TOD_EHIP;
@@ -1066,6 +1074,9 @@ tod_status tod_ctx_destroy(tod_ctx ctx) {
     }
     for (auto &e : ctx->ev)
         if (e) (void)hipEventDestroy(e);
+    for (auto &e : ctx->cg_ev)
+        if (e) (void)hipEventDestroy(e);
+    if (ctx->h_count) (void)hipHostFree(ctx->h_count);
     for (auto &r : ctx->recs) {
         (void)hipEventDestroy(r.a);
         (void)hipEventDestroy(r.b);
@@ -1311,11 +1322,6 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     int32_t *act = (int32_t *)ctx->cg_act.p, *count = (int32_t *)ctx->cg_count.p;
     c3::CgState *cs = (c3::CgState *)ctx->cg_state.p;
     const double tol2 = tol * tol;
-    auto fin = [&](int step, const int2 *seg_tiles) -> hipError_t {
-        KTimer kt(ctx, K_CG, st);
-        return c3::launch_cg_finish(st, nseg, seg_tiles, (const double *)ctx->cg_part.p, cs, act, step, tol2,
-                                    max_iter, count);
-    };
     auto vec = [&](int op, const c3::CgVecArgs &va) -> hipError_t {
         KTimer kt(ctx, K_CG, st);
         return c3::launch_cg_vec(st, mixed, op, va);
@@ -1399,9 +1405,9 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
             const int64_t j0 = nt ? base[t] : 0;
             t += nt;
             seg_gt[sgi].x = (int)gt.size();
-            for (int64_t o = 0; o < m; o += C3_CG_TILE) {
+            for (int64_t o = 0; o < m; o += C3_GAP_TILE) {
                 const int64_t j = j0 + o;
-                gt.push_back(make_int4(sgi, (int)(j & 0x7FFFFFFF), (int)std::min<int64_t>(C3_CG_TILE, m - o),
+                gt.push_back(make_int4(sgi, (int)(j & 0x7FFFFFFF), (int)std::min<int64_t>(C3_GAP_TILE, m - o),
                                        (int)(j >> 31)));
             }
             seg_gt[sgi].y = (int)gt.size() - seg_gt[sgi].x;
@@ -1415,7 +1421,7 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     HIPCHK(ctx->cg_y.ensure((size_t)total * 8 + 64));
     HIPCHK(ctx->cg_rho.ensure((size_t)total * 8 + 64));
     HIPCHK(ctx->cg_p.ensure((size_t)total * 8 + 64));
-    HIPCHK(ctx->cg_part.ensure(std::max<size_t>(P->ncg, gt.size()) * 8 + 64));
+    HIPCHK(ctx->cg_part.ensure(std::max<size_t>(P->ncg, 2 * gt.size()) * 8 + 64));
     v.part = (double *)ctx->cg_part.p;
     HIPCHK(ctx->cg_gap_tiles.upload(gt, st));
     HIPCHK(ctx->cg_seg_gap_tiles.upload(seg_gt, st));
@@ -1433,26 +1439,35 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     gv.y = (double *)ctx->cg_y.p;
     gv.rho = (double *)ctx->cg_rho.p;
     gv.p = (double *)ctx->cg_p.p;
-    const int2 *gseg = (const int2 *)ctx->cg_seg_gap_tiles.p;
+    gv.seg_tiles = (const int2 *)ctx->cg_seg_gap_tiles.p;
+    gv.tol2 = tol2;
+    gv.max_iter = max_iter;
+    gv.count = count;
     HIPCHK(vec(c3::CG_OP_GAP_START, gv));
-    HIPCHK(fin(c3::CG_RZ0, gseg));
-    gv.scatter_src = gv.p;
-    HIPCHK(vec(c3::CG_OP_GAP_SCATTER, gv));
+    {
+        KTimer kt(ctx, K_CG, st);
+        HIPCHK(c3::launch_cg_begin(st, nseg, gv));
+    }
     a.which = 1;  // M
     a.in_a = ctx->cg_fin.p;
     a.out = ctx->cg_fout.p;
     a.active = act;
+    // The count of active segments is read one iteration late, so that the device
+    // has the next one to run meanwhile: after the last, it finds every segment
+    // inactive and changes nothing.
     for (int it = 1; it <= max_iter; ++it) {
+        const int slot = it % C3_CG_SLOTS;
         if ((r = run_fft(ctx, st, P, mixed, a, 3)) != TOD_OK) return r;  // M S p
+        gv.it = it;
         HIPCHK(vec(c3::CG_OP_GAP_PQ, gv));
-        HIPCHK(fin(c3::CG_ALPHA, gseg));
         HIPCHK(vec(c3::CG_OP_GAP_UPDATE, gv));
-        HIPCHK(fin(c3::CG_RES, gseg));
-        int32_t h = 0;
-        HIPCHK(hipMemcpyAsync(&h, count, sizeof(h), hipMemcpyDeviceToHost, st));
-        HIPCHK(hipStreamSynchronize(st));
-        if (h == 0) break;
         HIPCHK(vec(c3::CG_OP_GAP_DIR, gv));
+        HIPCHK(hipMemcpyAsync(ctx->h_count + slot, count + slot, sizeof(int32_t), hipMemcpyDeviceToHost, st));
+        HIPCHK(hipEventRecord(ctx->cg_ev[it & 1], st));
+        if (it > 1) {
+            HIPCHK(hipEventSynchronize(ctx->cg_ev[(it - 1) & 1]));
+            if (ctx->h_count[(it - 1) % C3_CG_SLOTS] == 0) break;
+        }
     }
     // x = x0 + M S y where the segment has masked samples
     c3::CgVecArgs fv = gv;

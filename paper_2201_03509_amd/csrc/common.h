@@ -317,33 +317,39 @@ hipError_t launch_chisq_finish(hipStream_t st, const LayoutDev &L, const double 
 hipError_t launch_set_u64(hipStream_t st, uint64_t *p, uint64_t a, uint64_t b);
 
 // ---- masked n_corr draw (gapfill.hip): per-segment CG state and vector passes
-#define C3_CG_TILE 4096      // entries per elementwise tile (extended reals or gap entries)
+#define C3_CG_TILE 4096      // extended reals per elementwise tile
+#define C3_GAP_TILE 1024     // entries of the gap list per tile: four a thread
 struct CgState {
     double bb;       // rho_0 . rho_0: the stopping rule's reference
-    double alpha, beta;
-    double rr;       // rho . rho of the current residual
+    double rr[2];    // rho . rho after iteration it in rr[it & 1]
     int32_t iters;   // CG iterations done
     int32_t converged;
 };
-enum CgStep { CG_RZ0 = 0, CG_ALPHA, CG_RES };
 enum CgOp {
     CG_OP_INIT = 0,     // mu u -> res (b without its F^H W2 term)     (extended tiles)
     CG_OP_GAP_COUNT,    // masked positions per extended tile -> cnt  (extended tiles)
     CG_OP_GAP_FILL,     // their global extended indices -> gap_idx   (extended tiles)
-    CG_OP_GAP_START,    // y = 0, rho = p = x0[gap], partial rho.rho  (gap tiles)
+    CG_OP_GAP_START,    // y = 0, rho = p = fin[gap] = x0[gap], partial rho.rho (gap tiles)
     CG_OP_GAP_SCATTER,  // fin[gap] = scatter_src                     (gap tiles)
     CG_OP_GAP_PQ,       // partial p.q, q = sigma0^2 p - fout[gap]    (gap tiles)
     CG_OP_GAP_UPDATE,   // y += alpha p, rho -= alpha q, partial rho.rho (gap tiles)
-    CG_OP_GAP_DIR,      // p = rho + beta p, fin[gap] = p             (gap tiles)
+    CG_OP_GAP_DIR,      // p = rho + beta p, fin[gap] = p, stopping rule (gap tiles)
     CG_OP_CROP          // out = (x0 + fout)[0:n]                     (sample tiles)
 };
+#define C3_CG_SLOTS 4               // counters of active segments, one an iteration in turn
 struct CgVecArgs {
     const int4 *tiles;          // extended tiles (seg, first real, length, 0), gap tiles
     int ntile;                  // (seg, first entry low 31 bits, length, high bits) or
                                 // sample tiles, by operation
     const SegInfo *segs;
-    const int32_t *act;         // per segment: still iterating
-    const CgState *cs;
+    int32_t *act;               // per segment: still iterating
+    CgState *cs;
+    const int2 *seg_tiles;      // gap tiles of each segment (first, number)
+    int it;                     // iteration, from 1
+    double tol2;                // DIR: stopping rule
+    int max_iter;
+    int32_t *count;             // DIR: segments going on after iteration it are counted into
+                                //   count[it % C3_CG_SLOTS], the next slot is zeroed
     const void *d;              // INIT: residual d - s and the mask (per sample)
     int d_f64;
     const void *s;
@@ -362,16 +368,15 @@ struct CgVecArgs {
     double *y, *rho, *p;        // small system (FP64)
     const double *scatter_src;  // GAP_SCATTER source
     const int32_t *has_gap;     // CROP: segment has masked samples
-    double *part;               // per-tile partial sums
+    double *part;               // per-tile partial sums: of p.q (START: rho.rho), then of rho.rho
     void *out;                  // CROP: n_corr per sample
 };
 hipError_t launch_cg_vec(hipStream_t st, int mixed, int op, const CgVecArgs &a);
 // zero n elements of a vector of the transform type (a fill kernel)
 hipError_t launch_cg_zero(hipStream_t st, int mixed, void *v, int64_t n);
-// step: see CgStep; the CG_RES step counts still-active segments into *nactive
-// (zeroed by the CG_ALPHA step of the same iteration)
-hipError_t launch_cg_finish(hipStream_t st, int nseg, const int2 *seg_tiles, const double *part, CgState *cs,
-                            int32_t *act, int step, double tol2, int max_iter, int32_t *nactive);
+// state of every segment from the partial sums of GAP_START (no gap tiles: nothing
+// masked, x0 is the solution); zeroes the counters
+hipError_t launch_cg_begin(hipStream_t st, int nseg, const CgVecArgs &a);
 // iterations per segment (negative: stopped at max_iter before the tolerance)
 hipError_t launch_cg_iters(hipStream_t st, int nseg, const CgState *cs, int32_t *out);
 

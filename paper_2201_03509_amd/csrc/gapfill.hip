@@ -24,8 +24,8 @@
 // of each) in the transform's type.  The small system's vectors (y, rho, p)
 // are FP64, one entry per masked extended position, listed per segment in
 // gap_idx (global extended indices, ascending).  Elementwise kernels walk
-// tiles of one segment; a tile writes one partial sum, and one wave per
-// segment adds its tiles' partials in a fixed order (reproducible, no atomics
+// tiles of one segment; a tile writes one partial sum, and the reader of a
+// segment's sum adds its tiles' partials in a fixed order (reproducible, no atomics
 // on the sums).
 #include "common.h"
 
@@ -154,18 +154,20 @@ __global__ __launch_bounds__(C3_NT) void k_gap_fill(const int4 *__restrict__ til
     }
 }
 
-// rho = p = x0 at the masked positions, y = 0; partial sums of rho^2
+// rho = p = x0 at the masked positions, y = 0, and p in fin for the first
+// product; partial sums of rho^2
 template <typename T>
 __global__ __launch_bounds__(C3_NT) void k_gap_start(const int4 *__restrict__ gtiles, const int64_t *__restrict__ gap_idx,
                                                      const T *__restrict__ x0, double *__restrict__ y,
                                                      double *__restrict__ rho, double *__restrict__ p,
-                                                     double *__restrict__ part) {
+                                                     T *__restrict__ fin, double *__restrict__ part) {
     const int4 tl = gtiles[blockIdx.x];
     const int64_t j0 = gap_first(tl);
     double acc = 0;
     for (int i = threadIdx.x; i < tl.z; i += C3_NT) {
-        const int64_t j = j0 + i;
-        const double v = (double)x0[gap_idx[j]];
+        const int64_t j = j0 + i, g = gap_idx[j];
+        const double v = (double)x0[g];
+        fin[g] = x0[g];
         y[j] = 0.0;
         rho[j] = v;
         p[j] = v;
@@ -185,6 +187,25 @@ __global__ __launch_bounds__(C3_NT) void k_gap_scatter(const int4 *__restrict__ 
     for (int i = threadIdx.x; i < tl.z; i += C3_NT) fin[gap_idx[j0 + i]] = (T)src[j0 + i];
 }
 
+// The vector part of an iteration is three kernels, one per pass over the gap
+// list.  The scalars between them (alpha, then beta and the stopping rule) come
+// from every tile's partial sum of the segment, and each block adds these up for
+// itself, in the same fixed order in every wave: kernels of their own for the
+// scalars cost more than the additions, 52 us an iteration as five launches and
+// 17 as three (32 segments of 27000 masked positions).  One block per segment for
+// all of it took 46: a single CU moves the 3 MB no faster.
+
+// sum of a segment's tile partials, the same in every lane
+__device__ __forceinline__ double seg_total(const double *__restrict__ part, int2 tr) {
+    double v = 0;
+    for (int i = threadIdx.x & 63; i < tr.y; i += 64) v += part[tr.x + i];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    return v;
+}
+
+constexpr int kPer = C3_GAP_TILE / C3_NT;  // entries a thread holds
+
 // q = sigma0^2 p - (M S p) at the masked positions; partial sums of p . q
 template <typename T>
 __global__ __launch_bounds__(C3_NT) void k_gap_pq(const int4 *__restrict__ gtiles, const int32_t *__restrict__ act,
@@ -195,103 +216,131 @@ __global__ __launch_bounds__(C3_NT) void k_gap_pq(const int4 *__restrict__ gtile
     if (!act[tl.x]) return;
     const double s2 = sigma0[tl.x] * sigma0[tl.x];
     const int64_t j0 = gap_first(tl);
-    double acc = 0;
-    for (int i = threadIdx.x; i < tl.z; i += C3_NT) {
-        const int64_t j = j0 + i;
-        const double pv = p[j];
-        acc += pv * (s2 * pv - (double)fout[gap_idx[j]]);
+    double pv[kPer];
+    T f[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x + u * C3_NT;
+        const int64_t j = j0 + (i < tl.z ? i : 0);
+        pv[u] = i < tl.z ? p[j] : 0.0;
+        f[u] = fout[gap_idx[j]];
     }
+    double acc = 0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) acc += pv[u] * (s2 * pv[u] - (double)f[u]);
     block_sum(acc, part);
 }
 
-// y += alpha p; rho -= alpha q; partial sums of rho^2
+// alpha = rho . rho / p . q; y += alpha p; rho -= alpha q; partial sums of rho^2
 template <typename T>
 __global__ __launch_bounds__(C3_NT) void k_gap_update(const int4 *__restrict__ gtiles, const int32_t *__restrict__ act,
-                                                      const CgState *__restrict__ cs, const int64_t *__restrict__ gap_idx,
+                                                      const CgState *__restrict__ cs,
+                                                      const int2 *__restrict__ seg_tiles, int it,
+                                                      const int64_t *__restrict__ gap_idx,
                                                       const double *__restrict__ sigma0, const double *__restrict__ p,
                                                       const T *__restrict__ fout, double *__restrict__ y,
-                                                      double *__restrict__ rho, double *__restrict__ part) {
+                                                      double *__restrict__ rho, const double *__restrict__ part_pq,
+                                                      double *__restrict__ part_rr) {
     const int4 tl = gtiles[blockIdx.x];
     if (!act[tl.x]) return;
     const double s2 = sigma0[tl.x] * sigma0[tl.x];
-    const double al = cs[tl.x].alpha;
     const int64_t j0 = gap_first(tl);
+    double pv[kPer], yv[kPer], rv[kPer];
+    T f[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x + u * C3_NT;
+        const int64_t j = j0 + (i < tl.z ? i : 0);
+        pv[u] = p[j];
+        yv[u] = y[j];
+        rv[u] = rho[j];
+        f[u] = fout[gap_idx[j]];
+    }
+    const double pq = seg_total(part_pq, seg_tiles[tl.x]);
+    if (!(pq > 0.0)) return;  // breakdown (the small system is positive definite): DIR stops the segment
+    const double al = cs[tl.x].rr[(it - 1) & 1] / pq;
     double acc = 0;
-    for (int i = threadIdx.x; i < tl.z; i += C3_NT) {
-        const int64_t j = j0 + i;
-        const double pv = p[j];
-        const double q = s2 * pv - (double)fout[gap_idx[j]];
-        y[j] += al * pv;
-        const double r = rho[j] - al * q;
-        rho[j] = r;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x + u * C3_NT;
+        if (i >= tl.z) continue;
+        y[j0 + i] = yv[u] + al * pv[u];
+        const double r = rv[u] - al * (s2 * pv[u] - (double)f[u]);
+        rho[j0 + i] = r;
         acc += r * r;
     }
-    block_sum(acc, part);
+    block_sum(acc, part_rr);
 }
 
-// p = rho + beta p, scattered into fin for the next product
+// the stopping rule; where the segment goes on, p = rho + beta p, scattered into
+// fin for the next product.  The segment's first block writes its state: the
+// others read rr[(it - 1) & 1] alone of it, and act only falls for a segment that
+// each block finds stopped by itself.
 template <typename T>
-__global__ __launch_bounds__(C3_NT) void k_gap_dir(const int4 *__restrict__ gtiles, const int32_t *__restrict__ act,
-                                                   const CgState *__restrict__ cs, const int64_t *__restrict__ gap_idx,
+__global__ __launch_bounds__(C3_NT) void k_gap_dir(const int4 *__restrict__ gtiles, int32_t *act, CgState *cs,
+                                                   const int2 *__restrict__ seg_tiles, int it, double tol2,
+                                                   int max_iter, int32_t *__restrict__ count,
+                                                   const int64_t *__restrict__ gap_idx,
                                                    const double *__restrict__ rho, double *__restrict__ p,
-                                                   T *__restrict__ fin) {
+                                                   const double *__restrict__ part_pq,
+                                                   const double *__restrict__ part_rr, T *__restrict__ fin) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) count[(it + 1) % C3_CG_SLOTS] = 0;
     const int4 tl = gtiles[blockIdx.x];
     if (!act[tl.x]) return;
-    const double be = cs[tl.x].beta;
     const int64_t j0 = gap_first(tl);
-    for (int i = threadIdx.x; i < tl.z; i += C3_NT) {
-        const int64_t j = j0 + i;
-        const double v = rho[j] + be * p[j];
-        p[j] = v;
-        fin[gap_idx[j]] = (T)v;
+    double pv[kPer], rv[kPer];
+    int64_t g[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x + u * C3_NT;
+        const int64_t j = j0 + (i < tl.z ? i : 0);
+        pv[u] = p[j];
+        rv[u] = rho[j];
+        g[u] = gap_idx[j];
+    }
+    const int2 tr = seg_tiles[tl.x];
+    const bool first = (int)blockIdx.x == tr.x && threadIdx.x == 0;
+    CgState *c = cs + tl.x;
+    if (!(seg_total(part_pq, tr) > 0.0)) {
+        if (first) act[tl.x] = 0;
+        return;
+    }
+    const double rr0 = c->rr[(it - 1) & 1], rr = seg_total(part_rr, tr);
+    const bool converged = rr <= tol2 * c->bb, go = !converged && it < max_iter;
+    if (first) {
+        c->rr[it & 1] = rr;
+        c->iters = it;
+        c->converged = converged;
+        if (go)
+            atomicAdd(&count[it % C3_CG_SLOTS], 1);
+        else
+            act[tl.x] = 0;
+    }
+    if (!go) return;
+    const double be = rr0 != 0.0 ? rr / rr0 : 0.0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = threadIdx.x + u * C3_NT;
+        if (i >= tl.z) continue;
+        const double v = rv[u] + be * pv[u];
+        p[j0 + i] = v;
+        fin[g[u]] = (T)v;
     }
 }
 
-// one wave per segment: add the segment's tile partials in order, then step
-// the scalar recurrence (see CgStep)
-__global__ __launch_bounds__(C3_NT) void k_cg_finish(int nseg, const int2 *__restrict__ seg_tiles,
-                                                     const double *__restrict__ part, CgState *__restrict__ cs,
-                                                     int32_t *__restrict__ act, int step, double tol2, int max_iter,
-                                                     int32_t *__restrict__ nactive) {
+// one wave per segment: the state before the first iteration
+__global__ __launch_bounds__(C3_NT) void k_cg_begin(int nseg, const int2 *__restrict__ seg_tiles,
+                                                    const double *__restrict__ part, CgState *__restrict__ cs,
+                                                    int32_t *__restrict__ act, int32_t *__restrict__ count) {
     const int seg = blockIdx.x * (C3_NT / 64) + (threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    if (step == CG_ALPHA && blockIdx.x == 0 && threadIdx.x == 0) *nactive = 0;  // counted by CG_RES
+    if (blockIdx.x == 0 && threadIdx.x < C3_CG_SLOTS) count[threadIdx.x] = 0;
     if (seg >= nseg) return;
-    if (step != CG_RZ0 && !act[seg]) return;
     const int2 tr = seg_tiles[seg];
-    double v = 0;
-    for (int i = lane; i < tr.y; i += 64) v += part[tr.x + i];
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
-    if (lane != 0) return;
-    CgState c = cs[seg];
-    switch (step) {
-    case CG_RZ0:  // v = rho . rho at y = 0 (gap tiles; none: nothing masked)
-        c.alpha = c.beta = 0;
-        c.rr = c.bb = v;
-        c.iters = 0;
-        c.converged = (tr.y == 0 || v == 0.0) ? 1 : 0;  // x0 is the solution
-        act[seg] = c.converged ? 0 : 1;
-        break;
-    case CG_ALPHA:  // v = p . q
-        c.alpha = v > 0.0 ? c.rr / v : 0.0;
-        if (!(v > 0.0)) act[seg] = 0;  // breakdown: the small system is positive definite
-        break;
-    case CG_RES:  // v = rho . rho after the update
-        c.iters += 1;
-        if (v <= tol2 * c.bb) {
-            c.converged = 1;
-            act[seg] = 0;
-        } else if (c.iters >= max_iter) {
-            act[seg] = 0;
-        } else {
-            c.beta = c.rr != 0.0 ? v / c.rr : 0.0;
-            atomicAdd(nactive, 1);
-        }
-        c.rr = v;
-        break;
-    }
-    cs[seg] = c;
+    const double v = seg_total(part, tr);
+    if ((threadIdx.x & 63) != 0) return;
+    const int done = tr.y == 0 || v == 0.0;  // x0 is the solution
+    cs[seg] = CgState{v, {v, v}, 0, done};
+    act[seg] = !done;
 }
 
 // n_corr = (x0 + M S y)[0:n]: fout holds M S y where the segment has masked
@@ -356,7 +405,7 @@ hipError_t launch_cg_vec(hipStream_t st, int mixed, int op, const CgVecArgs &a) 
         break;                                                                                                \
     case CG_OP_GAP_START:                                                                                     \
         hipLaunchKernelGGL(k_gap_start<T>, g, b, 0, st, a.tiles, a.gap_idx, (const T *)a.x, a.y, a.rho, a.p,  \
-                           a.part);                                                                           \
+                           (T *)a.fin, a.part);                                                               \
         break;                                                                                                \
     case CG_OP_GAP_SCATTER:                                                                                   \
         hipLaunchKernelGGL(k_gap_scatter<T>, g, b, 0, st, a.tiles, a.act, a.gap_idx, a.scatter_src,           \
@@ -367,12 +416,12 @@ hipError_t launch_cg_vec(hipStream_t st, int mixed, int op, const CgVecArgs &a) 
                            (const T *)a.fout, a.part);                                                        \
         break;                                                                                                \
     case CG_OP_GAP_UPDATE:                                                                                    \
-        hipLaunchKernelGGL(k_gap_update<T>, g, b, 0, st, a.tiles, a.act, a.cs, a.gap_idx, a.sigma0, a.p,      \
-                           (const T *)a.fout, a.y, a.rho, a.part);                                            \
+        hipLaunchKernelGGL(k_gap_update<T>, g, b, 0, st, a.tiles, a.act, a.cs, a.seg_tiles, a.it, a.gap_idx,  \
+                           a.sigma0, a.p, (const T *)a.fout, a.y, a.rho, a.part, a.part + a.ntile);           \
         break;                                                                                                \
     case CG_OP_GAP_DIR:                                                                                       \
-        hipLaunchKernelGGL(k_gap_dir<T>, g, b, 0, st, a.tiles, a.act, a.cs, a.gap_idx, a.rho, a.p,            \
-                           (T *)a.fin);                                                                       \
+        hipLaunchKernelGGL(k_gap_dir<T>, g, b, 0, st, a.tiles, a.act, a.cs, a.seg_tiles, a.it, a.tol2,        \
+                           a.max_iter, a.count, a.gap_idx, a.rho, a.p, a.part, a.part + a.ntile, (T *)a.fin); \
         break;                                                                                                \
     case CG_OP_CROP:                                                                                          \
         hipLaunchKernelGGL(k_cg_crop<T>, g, b, 0, st, a.tiles, a.segs, a.has_gap, (const T *)a.x,             \
@@ -401,12 +450,11 @@ hipError_t launch_cg_zero(hipStream_t st, int mixed, void *v, int64_t n) {
     return hipGetLastError();
 }
 
-hipError_t launch_cg_finish(hipStream_t st, int nseg, const int2 *seg_tiles, const double *part, CgState *cs,
-                            int32_t *act, int step, double tol2, int max_iter, int32_t *nactive) {
+hipError_t launch_cg_begin(hipStream_t st, int nseg, const CgVecArgs &a) {
     if (nseg <= 0) return hipSuccess;
     const int per = C3_NT / 64;
-    hipLaunchKernelGGL(k_cg_finish, dim3((unsigned)((nseg + per - 1) / per)), dim3(C3_NT), 0, st, nseg, seg_tiles,
-                       part, cs, act, step, tol2, max_iter, nactive);
+    hipLaunchKernelGGL(k_cg_begin, dim3((unsigned)((nseg + per - 1) / per)), dim3(C3_NT), 0, st, nseg, a.seg_tiles,
+                       a.part, a.cs, a.act, a.count);
     return hipGetLastError();
 }
 
