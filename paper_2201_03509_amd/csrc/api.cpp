@@ -282,7 +282,16 @@ struct Pool {
         auto it = sub_tab.find(L);
         if (it != sub_tab.end()) return it->second;
         const int64_t off = (int64_t)re.size();
-        for (int64_t m = 0; m < L; ++m) push(m, L);
+        const auto row = row_tab.find((int)L);  // w_L^m = w_2L^2m, where those are there
+        for (int64_t m = 0; m < L; ++m) {
+            if (row == row_tab.end()) {
+                push(m, L);
+            } else {
+                const int64_t q = row->second.second + (2 * m < L ? 2 * m : 2 * m - L);
+                const long double sg = 2 * m < L ? 1.0L : -1.0L;
+                put(sg * re[q], sg * im[q]);
+            }
+        }
         sub_tab[L] = off;
         return off;
     }
@@ -292,7 +301,9 @@ struct Pool {
     }
     void push(int64_t m, int64_t L) {  // e^{-2 pi i m / L}
         const long double a = -2.0L * 3.14159265358979323846264338327950288L * (long double)m / (long double)L;
-        put(cosl(a), sinl(a));
+        long double s, c;
+        sincosl(a, &s, &c);
+        put(c, s);
     }
 };
 
@@ -425,6 +436,12 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
             fp.nr2 = (int)ch.r2.size();
             for (size_t i = 0; i < ch.r1.size(); ++i) fp.r1[i] = (int8_t)ch.r1[i];
             for (size_t i = 0; i < ch.r2.size(); ++i) fp.r2[i] = (int8_t)ch.r2[i];
+            fp.twr = fp.twh = -1;
+            if (c3rowc::compiled(ch.M2, !mixed)) {
+                const auto t = pool.add_row(ch.M2, !mixed);
+                fp.twr = t.first;
+                fp.twh = t.second;
+            }
             fp.tw1 = pool.add_sub(ch.M1);
             fp.tw2 = pool.add_sub(ch.M2);
             const int64_t N = 2 * M;
@@ -432,12 +449,6 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
             for (int64_t m = 0; m < 1024; ++m) pool.push(m, N);
             fp.twhi = (int64_t)pool.re.size();
             for (int64_t h = 0; h <= N / 1024 + 1; ++h) pool.push(h * 1024, N);
-            fp.twr = fp.twh = -1;
-            if (c3rowc::compiled(ch.M2, !mixed)) {
-                const auto t = pool.add_row(ch.M2, !mixed);
-                fp.twr = t.first;
-                fp.twh = t.second;
-            }
             P->plan_of_M[M] = (int)P->h_plans.size();
             P->h_plans.push_back(fp);
             it = P->plan_of_M.find(M);
@@ -906,6 +917,21 @@ tod_status get_bin_runs(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t
 // 385 without; with 9.4e8 samples 3.00 ms with and 3.28 without.
 bool map_records(const tod_layout *L) { return L->nsamp >= 16 * L->npix_total; }
 
+c3::BeginArgs begin_args(tod_ctx ctx, const double *sigma0, const double *fknee, const double *alpha, bool set_seed,
+                         uint64_t seed, uint64_t iter) {
+    c3::BeginArgs a;
+    memset(&a, 0, sizeof(a));
+    a.sigma0 = sigma0;
+    a.fknee = fknee;
+    a.alpha = alpha;
+    if (set_seed) {
+        a.seed_iter = (uint64_t *)ctx->d_seed_iter;
+        a.seed = seed;
+        a.iter = iter;
+    }
+    return a;
+}
+
 c3::FftArgs fft_args(tod_ctx ctx, Plan *P, const tod_layout *L) {
     c3::FftArgs a;
     memset(&a, 0, sizeof(a));
@@ -1260,8 +1286,7 @@ tod_status sample_ncorr(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const
     const int mixed = prec == TOD_MIXED;
     Plan *P;
     if ((r = get_plan(ctx, lay, mixed, &P)) != TOD_OK) return r;
-    HIPCHK(c3::launch_set_u64(ctx->stream, ctx->d_seed_iter, seed, iter));
-    HIPCHK(c3::launch_check_params(ctx->stream, make_layout_dev(lay), sigma0, fknee, alpha, ctx->d_err));
+    HIPCHK(c3::launch_begin(ctx->stream, make_layout_dev(lay), begin_args(ctx, sigma0, fknee, alpha, true, seed, iter), ctx->d_err));
     return ncorr_impl(ctx, lay, mixed, P, d, d_dtype, s, !mixed, sigma0, fknee, alpha, mean_only,
                       ncorr_out);
 }
@@ -1317,8 +1342,7 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     HIPCHK(ctx->cg_act.ensure((size_t)nseg * 4 + 64));
     HIPCHK(ctx->cg_count.ensure(64));
     hipStream_t st = ctx->stream;
-    HIPCHK(c3::launch_set_u64(st, ctx->d_seed_iter, seed, iter));
-    HIPCHK(c3::launch_check_params(st, make_layout_dev(lay), sigma0, fknee, alpha, ctx->d_err));
+    HIPCHK(c3::launch_begin(st, make_layout_dev(lay), begin_args(ctx, sigma0, fknee, alpha, true, seed, iter), ctx->d_err));
     int32_t *act = (int32_t *)ctx->cg_act.p, *count = (int32_t *)ctx->cg_count.p;
     c3::CgState *cs = (c3::CgState *)ctx->cg_state.p;
     const double tol2 = tol * tol;
@@ -1505,8 +1529,7 @@ tod_status sample_gain(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const 
     HIPCHK(ctx->gain_kd.ensure((size_t)lay->nsamp * esz + 64));
     HIPCHK(ctx->gain_part.ensure((size_t)P->nsample_tiles * sizeof(double2) + 64));
     hipStream_t st = ctx->stream;
-    HIPCHK(c3::launch_set_u64(st, ctx->d_seed_iter, seed, iter));
-    HIPCHK(c3::launch_check_params(st, make_layout_dev(lay), sigma0, fknee, alpha, ctx->d_err));
+    HIPCHK(c3::launch_begin(st, make_layout_dev(lay), begin_args(ctx, sigma0, fknee, alpha, true, seed, iter), ctx->d_err));
     c3::FftArgs a = fft_args(ctx, P, lay);
     a.sigma0 = sigma0;
     a.fknee = fknee;
@@ -1554,12 +1577,9 @@ tod_status sample_noise(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const
     HIPCHK(ctx->xi_bins.ensure(nbin * 8 + 64));
     HIPCHK(ctx->xi_part.ensure((size_t)P->nsample_tiles * 8 + 64));
     hipStream_t st = ctx->stream;
-    HIPCHK(c3::launch_set_u64(st, ctx->d_seed_iter, seed, iter));
-    HIPCHK(c3::launch_check_params(st, make_layout_dev(lay), nullptr, fknee_in, nullptr, ctx->d_err));
-    {
-        KTimer kt(ctx, K_NOISE, st);
-        HIPCHK(c3::launch_zero(st, ctx->xi_bins.p, (int64_t)(nbin * 8)));
-    }
+    c3::BeginArgs ba = begin_args(ctx, nullptr, fknee_in, nullptr, true, seed, iter);
+    ba.zero((double *)ctx->xi_bins.p, (int64_t)nbin);
+    HIPCHK(c3::launch_begin(st, make_layout_dev(lay), ba, ctx->d_err));
     {
         KTimer kt(ctx, K_NOISE, st);
         HIPCHK(c3::launch_xi_white(st, mixed, (const int4 *)P->sample_tiles.p, P->nsample_tiles, lay->seg_off, d,
@@ -1599,7 +1619,7 @@ tod_status bin_tod(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const int3
     int nt;
     if ((r = get_bin_runs(ctx, lay, P, pix, &tiles, &nt, &runs)) != TOD_OK) return r;
     const LayoutDev Ld = make_layout_dev(lay);
-    HIPCHK(c3::launch_check_params(ctx->stream, Ld, sigma0, nullptr, nullptr, ctx->d_err));
+    HIPCHK(c3::launch_begin(ctx->stream, Ld, begin_args(ctx, sigma0, nullptr, nullptr, false, 0, 0), ctx->d_err));
     if (!accumulate) HIPCHK(c3::launch_zero(ctx->stream, acc, lay->npix_total * 10 * sizeof(double)));
     KTimer kt(ctx, K_BIN, ctx->stream);
     HIPCHK(c3::launch_bin_tiles(ctx->stream, Ld, mixed, tiles, nt, P->run_rev, runs, pix, psi, d, d_dtype == TOD_F64, ncorr,
@@ -1638,8 +1658,11 @@ static tod_status chisq_common(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     HIPCHK(ctx->seg_sums.ensure(ssz));
     HIPCHK(ctx->seg_whittle.ensure(ssz));
     hipStream_t st = ctx->stream;
-    HIPCHK(c3::launch_zero(st, ctx->seg_sums.p, ssz));
-    HIPCHK(c3::launch_zero(st, ctx->seg_whittle.p, ssz));
+    c3::BeginArgs ba = begin_args(ctx, sigma0, fknee, alpha, false, 0, 0);
+    ba.zero((double *)ctx->seg_sums.p, (int64_t)(ssz / sizeof(double)));
+    ba.zero((double *)ctx->seg_whittle.p, (int64_t)(ssz / sizeof(double)));
+    for (double *g : {gsig, gfk, galpha})
+        if (g) ba.zero(g, lay->ndet);
     // the map gradient gathers in records of four where the maps are read so
     double *gm = grad_maps;
     if (grad_maps && map_records(lay)) {
@@ -1647,13 +1670,10 @@ static tod_status chisq_common(tod_ctx ctx, const tod_layout *lay, tod_prec prec
         gm = (double *)ctx->gmap4.p;
     }
     if (gm) HIPCHK(c3::launch_zero(st, gm, (int64_t)sizeof(double) * (gm == grad_maps ? 3 : 4) * lay->npix_total));
-    if (gsig) HIPCHK(c3::launch_zero(st, gsig, sizeof(double) * lay->ndet));
-    if (gfk) HIPCHK(c3::launch_zero(st, gfk, sizeof(double) * lay->ndet));
-    if (galpha) HIPCHK(c3::launch_zero(st, galpha, sizeof(double) * lay->ndet));
     const bool rec = map_records(lay);
     if (rec) HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
     const LayoutDev Ld = make_layout_dev(lay);
-    HIPCHK(c3::launch_check_params(st, Ld, sigma0, fknee, alpha, ctx->d_err));
+    HIPCHK(c3::launch_begin(st, Ld, ba, ctx->d_err));
     {
         KTimer kt(ctx, K_CHISQ, st);
         HIPCHK(c3::launch_chisq_time_tiles(st, Ld, mixed, (const int4 *)P->chisq.tiles.p, P->chisq.n, P->chisq.rev,
@@ -1783,18 +1803,19 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
     gk = fnv(gk, &d_dtype, sizeof(d_dtype));
     gk = fnv(gk, &mixed, sizeof(mixed));
 
-    HIPCHK(c3::launch_set_u64(st, ctx->d_seed_iter, seed, iter));
     const bool have_tiles = P->nbin > 0;
     if (use_graph && have_tiles) {
         auto it = ctx->graphs.find(gk);
         if (it != ctx->graphs.end()) {
+            HIPCHK(c3::launch_set_u64(st, ctx->d_seed_iter, seed, iter));
             HIPCHK(hipGraphLaunch(it->second.ex, st));
             return TOD_OK;
         }
     }
     // eager (or capture) sequence
     auto run = [&](bool capture) -> tod_status {
-        HIPCHK(c3::launch_check_params(st, Ld, sigma0, fknee, alpha, ctx->d_err));
+        // the seed and iteration number change between a graph's replays: set before it
+        HIPCHK(c3::launch_begin(st, Ld, begin_args(ctx, sigma0, fknee, alpha, !capture, seed, iter), ctx->d_err));
         {
             KTimer kt(ctx, K_DECODE, st);
             HIPCHK(c3::launch_decode(st, Ld, make_huff_dev(pix), make_huff_dev(psi),
@@ -1860,6 +1881,7 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
     ge.g = g;
     HIPCHK(hipGraphInstantiate(&ge.ex, g, nullptr, nullptr, 0));
     ctx->graphs[gk] = ge;
+    HIPCHK(c3::launch_set_u64(st, ctx->d_seed_iter, seed, iter));
     HIPCHK(hipGraphLaunch(ge.ex, st));
     return TOD_OK;
 }

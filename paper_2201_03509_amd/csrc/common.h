@@ -225,11 +225,27 @@ hipError_t launch_resid_tiles(hipStream_t st, const LayoutDev &L, int mixed, con
                               int ntile, int rev, const int32_t *pix, const uint16_t *psi, const void *d,
                               int d_f64, const void *maps, void *maps4, const double *gain,
                               const void *trig, void *r_out, uint32_t *err);
-// per non-empty segment: sigma0 > 0, f_knee > 0, alpha < 0, all finite (any
-// pointer may be NULL: not checked); failures set C3_ERR_SIGMA0 / _FKNEE /
-// _ALPHA in the sticky word.  The kernels that use them still run.
-hipError_t launch_check_params(hipStream_t st, const LayoutDev &L, const double *sigma0,
-                               const double *fknee, const double *alpha, uint32_t *err);
+// The small work before an entry point's first kernel, in one launch.  Per
+// non-empty segment: sigma0 > 0, f_knee > 0, alpha < 0, all finite (any pointer
+// may be NULL: not checked); failures set C3_ERR_SIGMA0 / _FKNEE / _ALPHA in the
+// sticky word, the kernels that use them still run.  {seed, iter} at seed_iter
+// (NULL: left), and up to five ranges of doubles zeroed.
+struct BeginArgs {
+    const double *sigma0, *fknee, *alpha;
+    uint64_t *seed_iter;
+    uint64_t seed, iter;
+    double *z[5];
+    int64_t nz[5];
+    void zero(double *p, int64_t n) {
+        for (int i = 0; i < 5; ++i)
+            if (!z[i]) {
+                z[i] = p;
+                nz[i] = n;
+                return;
+            }
+    }
+};
+hipError_t launch_begin(hipStream_t st, const LayoutDev &L, const BeginArgs &a, uint32_t *err);
 
 // FFT-based passes (modes: see launch_fft_pass)
 struct FftArgs {

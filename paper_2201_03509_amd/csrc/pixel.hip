@@ -393,11 +393,18 @@ __global__ __launch_bounds__(C3_NT) void k_gmap_out(int64_t npt, const double4 *
 }
 
 // per non-empty segment: the noise parameters the draws and weights divide by
-__global__ __launch_bounds__(C3_NT) void k_check_params(LayoutDev Ld, const double *__restrict__ sigma0,
-                                                        const double *__restrict__ fknee,
-                                                        const double *__restrict__ alpha,
-                                                        uint32_t *__restrict__ err) {
+// (One launch: each of its parts alone costs 4.5 us back to back, the chi^2 with
+// gradients had six of them.)
+__global__ __launch_bounds__(C3_NT) void k_begin(LayoutDev Ld, c3::BeginArgs a, uint32_t *__restrict__ err) {
     const int s = blockIdx.x * C3_NT + threadIdx.x;
+    if (s == 0 && a.seed_iter) {
+        a.seed_iter[0] = a.seed;
+        a.seed_iter[1] = a.iter;
+    }
+#pragma unroll
+    for (int j = 0; j < 5; ++j)
+        for (int64_t i = s; i < a.nz[j]; i += (int64_t)gridDim.x * C3_NT) a.z[j][i] = 0.0;
+    const double *sigma0 = a.sigma0, *fknee = a.fknee, *alpha = a.alpha;
     if (s >= Ld.nseg || Ld.seg_off[s + 1] <= Ld.seg_off[s]) return;
     uint32_t e = 0;
     if (sigma0) {
@@ -774,11 +781,17 @@ hipError_t launch_resid_tiles(hipStream_t st, const LayoutDev &L, int mixed, con
     return hipGetLastError();
 }
 
-hipError_t launch_check_params(hipStream_t st, const LayoutDev &L, const double *sigma0, const double *fknee,
-                               const double *alpha, uint32_t *err) {
-    if (L.nseg <= 0 || (!sigma0 && !fknee && !alpha)) return hipSuccess;
-    const int nb = (L.nseg + C3_NT - 1) / C3_NT;
-    hipLaunchKernelGGL(k_check_params, dim3(nb), dim3(C3_NT), 0, st, L, sigma0, fknee, alpha, err);
+hipError_t launch_begin(hipStream_t st, const LayoutDev &L, const BeginArgs &a, uint32_t *err) {
+    int64_t n = a.sigma0 || a.fknee || a.alpha ? L.nseg : 0;
+    if (a.seed_iter) n = n > 1 ? n : 1;
+    int64_t most = 0;
+    for (int j = 0; j < 5; ++j) most = a.nz[j] > most ? a.nz[j] : most;
+    if (most > (int64_t)4096 * C3_NT) most = (int64_t)4096 * C3_NT;  // grid-stride beyond
+    if (n < most) n = most;
+    if (n <= 0) return hipSuccess;
+    LayoutDev l = L;
+    if (!a.sigma0 && !a.fknee && !a.alpha) l.nseg = 0;
+    hipLaunchKernelGGL(k_begin, dim3((unsigned)((n + C3_NT - 1) / C3_NT)), dim3(C3_NT), 0, st, l, a, err);
     return hipGetLastError();
 }
 
