@@ -150,7 +150,7 @@ struct tod_ctx_s {
     // masked n_corr solver: Krylov vectors and the transform output (the
     // precision's type), partial sums, per-segment state, active flags and the
     // active-segment count
-    DevBuf cg_x, cg_res, cg_fin, cg_fout, cg_part, cg_state, cg_act, cg_count, cg_has_gap;
+    DevBuf cg_x, cg_res, cg_fin, cg_fout, cg_part, cg_state, cg_act, cg_has_gap;
     DevBuf cg_cnt, cg_base, cg_gap_idx, cg_y, cg_rho, cg_p, cg_gap_tiles, cg_seg_gap_tiles;
     // gain draw: filtered template and data (per sample), per-tile partial sums
     DevBuf gain_kt, gain_kd, gain_part;
@@ -166,8 +166,8 @@ struct tod_ctx_s {
     uint32_t last_err_bits = 0;
     bool timing = false;
     hipEvent_t ev[8] = {};                 // scratch events (autotuning)
-    int32_t *h_count = nullptr;            // masked draw: active segments of the last iterations (pinned)
-    hipEvent_t cg_ev[2] = {};              //   copied
+    int32_t *h_go_on = nullptr;            // masked draw: a segment goes on after an iteration (pinned)
+    hipEvent_t cg_ev[2] = {};              //   the last two iterations done
     std::vector<hipEvent_t> ev_pool;       // recycled timing events
     struct Rec {
         int kid;
@@ -1072,7 +1072,7 @@ tod_status tod_ctx_create(tod_ctx *out, int device, void *hip_stream) {
         return TOD_EHIP;
     }
     for (auto &e : ctx->ev) (void)hipEventCreate(&e);
-    bool cg_ok = hipHostMalloc((void **)&ctx->h_count, 64) == hipSuccess;
+    bool cg_ok = hipHostMalloc((void **)&ctx->h_go_on, 64) == hipSuccess;
     for (auto &e : ctx->cg_ev) cg_ok = cg_ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
     if (!cg_ok) {
         delete ctx;
@@ -1102,7 +1102,7 @@ tod_status tod_ctx_destroy(tod_ctx ctx) {
         if (e) (void)hipEventDestroy(e);
     for (auto &e : ctx->cg_ev)
         if (e) (void)hipEventDestroy(e);
-    if (ctx->h_count) (void)hipHostFree(ctx->h_count);
+    if (ctx->h_go_on) (void)hipHostFree(ctx->h_go_on);
     for (auto &r : ctx->recs) {
         (void)hipEventDestroy(r.a);
         (void)hipEventDestroy(r.b);
@@ -1340,10 +1340,9 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     HIPCHK(ctx->cg_base.ensure((size_t)P->ncg * 8 + 64));
     HIPCHK(ctx->cg_state.ensure((size_t)nseg * sizeof(c3::CgState) + 64));
     HIPCHK(ctx->cg_act.ensure((size_t)nseg * 4 + 64));
-    HIPCHK(ctx->cg_count.ensure(64));
     hipStream_t st = ctx->stream;
     HIPCHK(c3::launch_begin(st, make_layout_dev(lay), begin_args(ctx, sigma0, fknee, alpha, true, seed, iter), ctx->d_err));
-    int32_t *act = (int32_t *)ctx->cg_act.p, *count = (int32_t *)ctx->cg_count.p;
+    int32_t *act = (int32_t *)ctx->cg_act.p;
     c3::CgState *cs = (c3::CgState *)ctx->cg_state.p;
     const double tol2 = tol * tol;
     auto vec = [&](int op, const c3::CgVecArgs &va) -> hipError_t {
@@ -1466,7 +1465,7 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     gv.seg_tiles = (const int2 *)ctx->cg_seg_gap_tiles.p;
     gv.tol2 = tol2;
     gv.max_iter = max_iter;
-    gv.count = count;
+    HIPCHK(hipHostGetDevicePointer((void **)&gv.go_on, ctx->h_go_on, 0));
     HIPCHK(vec(c3::CG_OP_GAP_START, gv));
     {
         KTimer kt(ctx, K_CG, st);
@@ -1476,21 +1475,23 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     a.in_a = ctx->cg_fin.p;
     a.out = ctx->cg_fout.p;
     a.active = act;
-    // The count of active segments is read one iteration late, so that the device
+    // Whether any segment goes on is read one iteration late, so that the device
     // has the next one to run meanwhile: after the last, it finds every segment
-    // inactive and changes nothing.
+    // inactive and changes nothing.  The kernel sets the flag in host memory (a
+    // copy of a counter was a launch more, 3 us); a slot is cleared here before
+    // its iteration is enqueued, when its last use has been waited for.
     for (int it = 1; it <= max_iter; ++it) {
-        const int slot = it % C3_CG_SLOTS;
+        volatile int32_t *flag = ctx->h_go_on;
+        flag[it % C3_CG_SLOTS] = 0;
         if ((r = run_fft(ctx, st, P, mixed, a, 3)) != TOD_OK) return r;  // M S p
         gv.it = it;
         HIPCHK(vec(c3::CG_OP_GAP_PQ, gv));
         HIPCHK(vec(c3::CG_OP_GAP_UPDATE, gv));
         HIPCHK(vec(c3::CG_OP_GAP_DIR, gv));
-        HIPCHK(hipMemcpyAsync(ctx->h_count + slot, count + slot, sizeof(int32_t), hipMemcpyDeviceToHost, st));
         HIPCHK(hipEventRecord(ctx->cg_ev[it & 1], st));
         if (it > 1) {
             HIPCHK(hipEventSynchronize(ctx->cg_ev[(it - 1) & 1]));
-            if (ctx->h_count[(it - 1) % C3_CG_SLOTS] == 0) break;
+            if (flag[(it - 1) % C3_CG_SLOTS] == 0) break;
         }
     }
     // x = x0 + M S y where the segment has masked samples

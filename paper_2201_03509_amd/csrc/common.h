@@ -352,7 +352,7 @@ enum CgOp {
     CG_OP_GAP_DIR,      // p = rho + beta p, fin[gap] = p, stopping rule (gap tiles)
     CG_OP_CROP          // out = (x0 + fout)[0:n]                     (sample tiles)
 };
-#define C3_CG_SLOTS 4               // counters of active segments, one an iteration in turn
+#define C3_CG_SLOTS 4               // flags of iterations to come, used in turn
 struct CgVecArgs {
     const int4 *tiles;          // extended tiles (seg, first real, length, 0), gap tiles
     int ntile;                  // (seg, first entry low 31 bits, length, high bits) or
@@ -364,8 +364,8 @@ struct CgVecArgs {
     int it;                     // iteration, from 1
     double tol2;                // DIR: stopping rule
     int max_iter;
-    int32_t *count;             // DIR: segments going on after iteration it are counted into
-                                //   count[it % C3_CG_SLOTS], the next slot is zeroed
+    int32_t *go_on;             // DIR: go_on[it % C3_CG_SLOTS] = 1 where a segment goes on after
+                                //   iteration it (host memory)
     const void *d;              // INIT: residual d - s and the mask (per sample)
     int d_f64;
     const void *s;
@@ -391,7 +391,7 @@ hipError_t launch_cg_vec(hipStream_t st, int mixed, int op, const CgVecArgs &a);
 // zero n elements of a vector of the transform type (a fill kernel)
 hipError_t launch_cg_zero(hipStream_t st, int mixed, void *v, int64_t n);
 // state of every segment from the partial sums of GAP_START (no gap tiles: nothing
-// masked, x0 is the solution); zeroes the counters
+// masked, x0 is the solution)
 hipError_t launch_cg_begin(hipStream_t st, int nseg, const CgVecArgs &a);
 // iterations per segment (negative: stopped at max_iter before the tolerance)
 hipError_t launch_cg_iters(hipStream_t st, int nseg, const CgState *cs, int32_t *out);

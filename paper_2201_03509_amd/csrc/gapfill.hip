@@ -279,12 +279,11 @@ __global__ __launch_bounds__(C3_NT) void k_gap_update(const int4 *__restrict__ g
 template <typename T>
 __global__ __launch_bounds__(C3_NT) void k_gap_dir(const int4 *__restrict__ gtiles, int32_t *act, CgState *cs,
                                                    const int2 *__restrict__ seg_tiles, int it, double tol2,
-                                                   int max_iter, int32_t *__restrict__ count,
+                                                   int max_iter, int32_t *__restrict__ go_on,
                                                    const int64_t *__restrict__ gap_idx,
                                                    const double *__restrict__ rho, double *__restrict__ p,
                                                    const double *__restrict__ part_pq,
                                                    const double *__restrict__ part_rr, T *__restrict__ fin) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) count[(it + 1) % C3_CG_SLOTS] = 0;
     const int4 tl = gtiles[blockIdx.x];
     if (!act[tl.x]) return;
     const int64_t j0 = gap_first(tl);
@@ -312,7 +311,7 @@ __global__ __launch_bounds__(C3_NT) void k_gap_dir(const int4 *__restrict__ gtil
         c->iters = it;
         c->converged = converged;
         if (go)
-            atomicAdd(&count[it % C3_CG_SLOTS], 1);
+            go_on[it % C3_CG_SLOTS] = 1;
         else
             act[tl.x] = 0;
     }
@@ -331,9 +330,8 @@ __global__ __launch_bounds__(C3_NT) void k_gap_dir(const int4 *__restrict__ gtil
 // one wave per segment: the state before the first iteration
 __global__ __launch_bounds__(C3_NT) void k_cg_begin(int nseg, const int2 *__restrict__ seg_tiles,
                                                     const double *__restrict__ part, CgState *__restrict__ cs,
-                                                    int32_t *__restrict__ act, int32_t *__restrict__ count) {
+                                                    int32_t *__restrict__ act) {
     const int seg = blockIdx.x * (C3_NT / 64) + (threadIdx.x >> 6);
-    if (blockIdx.x == 0 && threadIdx.x < C3_CG_SLOTS) count[threadIdx.x] = 0;
     if (seg >= nseg) return;
     const int2 tr = seg_tiles[seg];
     const double v = seg_total(part, tr);
@@ -421,7 +419,7 @@ hipError_t launch_cg_vec(hipStream_t st, int mixed, int op, const CgVecArgs &a) 
         break;                                                                                                \
     case CG_OP_GAP_DIR:                                                                                       \
         hipLaunchKernelGGL(k_gap_dir<T>, g, b, 0, st, a.tiles, a.act, a.cs, a.seg_tiles, a.it, a.tol2,        \
-                           a.max_iter, a.count, a.gap_idx, a.rho, a.p, a.part, a.part + a.ntile, (T *)a.fin); \
+                           a.max_iter, a.go_on, a.gap_idx, a.rho, a.p, a.part, a.part + a.ntile, (T *)a.fin); \
         break;                                                                                                \
     case CG_OP_CROP:                                                                                          \
         hipLaunchKernelGGL(k_cg_crop<T>, g, b, 0, st, a.tiles, a.segs, a.has_gap, (const T *)a.x,             \
@@ -454,7 +452,7 @@ hipError_t launch_cg_begin(hipStream_t st, int nseg, const CgVecArgs &a) {
     if (nseg <= 0) return hipSuccess;
     const int per = C3_NT / 64;
     hipLaunchKernelGGL(k_cg_begin, dim3((unsigned)((nseg + per - 1) / per)), dim3(C3_NT), 0, st, nseg, a.seg_tiles,
-                       a.part, a.cs, a.act, a.count);
+                       a.part, a.cs, a.act);
     return hipGetLastError();
 }
 
