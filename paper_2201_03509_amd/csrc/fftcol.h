@@ -129,6 +129,18 @@ __device__ __forceinline__ void col_fwd(const FftArgs &a, const ColTask &sg) {
             x[j1] = csub(ext_pair<T>(ra, n, t), ext_pair<T>(rb, n, t));
             if ((j1 & 7) == 7) __builtin_amdgcn_sched_barrier(0);
         }
+    } else if constexpr (IN == 5) {
+        // r = in_a, FP32 data (FP64 transforms).  IN 3 branches on the type at each
+        // element, which keeps its loads apart: 19 columns of 256 lanes took 11.8
+        // us with it, 6 with the type compiled in.
+        const __amdgpu_buffer_rsrc_t r =
+            __builtin_amdgcn_make_buffer_rsrc((float *)a.in_a + sg.samp_off, 0, 4 * sg.n, C3_BUF_WORD3);
+#pragma unroll
+        for (int j1 = 0; j1 < M1; ++j1) {
+            const cx<float> u = ext_pair<float>(r, n, 2u * (uint32_t)(M2 * j1 + j2));
+            x[j1] = cx<T>{(T)u.x, (T)u.y};
+            if ((j1 & 15) == 15) __builtin_amdgcn_sched_barrier(0);
+        }
     } else if constexpr (IN == 4) {
         // r = in_a - in_b, FP32 data less an FP64 model (FP64 transforms)
         const __amdgpu_buffer_rsrc_t ra =
@@ -229,7 +241,7 @@ __device__ __forceinline__ void col_pass(const FftArgs &a, const ColTask &sg) {
 // the input form of the forward pass (col_fwd's IN)
 inline int col_input(const FftArgs &a, bool f64) {
     const bool own = !!a.in_a_f64 == f64 && (!a.in_b || !!a.in_b_f64 == f64);
-    if (f64 && !a.full_io && !a.in_a_f64 && a.in_b && a.in_b_f64) return 4;
+    if (f64 && !a.full_io && !a.in_a_f64 && (!a.in_b || a.in_b_f64)) return a.in_b ? 4 : 5;
     return a.full_io ? 0 : !own ? 3 : a.in_b ? 2 : 1;
 }
 

@@ -32,6 +32,7 @@ hipError_t launch_fft_col_reg_f64(hipStream_t st, const FftArgs &a, int pass) {
     else if (in == 1) hipLaunchKernelGGL((k_cold<0, 1>), g, b, 0, st, a);
     else if (in == 2) hipLaunchKernelGGL((k_cold<0, 2>), g, b, 0, st, a);
     else if (in == 4) hipLaunchKernelGGL((k_cold<0, 4>), g, b, 0, st, a);
+    else if (in == 5) hipLaunchKernelGGL((k_cold<0, 5>), g, b, 0, st, a);
     else hipLaunchKernelGGL((k_cold<0, 3>), g, b, 0, st, a);
     return hipGetLastError();
 }
