@@ -77,9 +77,10 @@ FAMILY_SOURCES = {
     "project": ["pixel.hip", "common.h"],
     "bin": ["pixel.hip", "common.h"],
     "zero": ["pixel.hip", "common.h"],
-    "fft_col_fwd": ["fftcol.hip", "fft.hip", "fftdev.h", "fftmode.h", "rng.h", "common.h"],
-    "fft_row": ["fft.hip", "rowc.hip", "rowc.h", "fftdev.h", "fftmode.h", "rng.h", "common.h"],
-    "fft_col_inv": ["fftcol.hip", "fft.hip", "fftdev.h", "fftmode.h", "rng.h", "common.h"],
+    "fft_col_fwd": ["fftcol.hip", "fftcol.h", "fftcold.hip", "fft.hip", "fftdev.h", "fftmode.h", "rng.h", "common.h"],
+    "fft_row": ["fft.hip", "rowc.hip", "rowc.h", "rowc_body.h", "rowl.hip", "rowbody.h", "rowd.h", "rowd.hip", "rows.hip", "fp64fn.h",
+                "fftdev.h", "fftmode.h", "rng.h", "common.h"],
+    "fft_col_inv": ["fftcol.hip", "fftcol.h", "fftcold.hip", "fft.hip", "fftdev.h", "fftmode.h", "rng.h", "common.h"],
 }
 
 

@@ -96,7 +96,8 @@ struct Plan {
     struct RowGroup {
         int lds;                          // dynamic LDS bytes of the launch
         int t0, nt;                       // range of the row task list
-        int rowc;                         // compiled rows: 1, 2 (wide registers), 3, 4 (FP64, short); 0: generic
+        int rowc;                         // compiled rows: 1, 2 (wide registers), 3, 4 (FP64, short), a row length
+                                          //   of its own launch; 0: generic
         bool pair_rows = false;           // rows the compiled kernel's pair tasks cover (not mode 3)
     };
     struct Batch {
@@ -522,6 +523,10 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
             // rows, four) to a CU
             const int rl = 2 * it->first * esz + (mixed ? 0 : c3d::kTab * esz);
             const int cls = !mixed ? (c3rowc::short_row(it->first) ? 4 : 3) : c3rowc::wide(it->first) ? 2 : 1;
+            if (mixed && it->second.size() >= C3_ROW_OWN) {  // a launch of its own: see rowl.hip
+                launches[{it->first, 0}] = {rl, it->second};
+                continue;
+            }
             auto &g = launches[{cls, std::min(mixed ? 3 : 2, C3_LDS_MAX / rl)}];
             g.first = std::max(g.first, rl);
             g.second.insert(g.second.end(), it->second.begin(), it->second.end());
@@ -1011,7 +1016,8 @@ tod_status run_fft(tod_ctx ctx, hipStream_t st, Plan *P, int mixed, const c3::Ff
                     ag.row_lds = g.lds;
                     KTimer kt(ctx, K_ROW, st);
                     if (g.rowc && c3::rowc_supported(a.mode))
-                        HIPCHK(g.rowc == 4   ? c3::launch_rows(st, ag)
+                        HIPCHK(g.rowc > 4    ? c3::launch_rowl(st, ag, g.rowc)
+                               : g.rowc == 4 ? c3::launch_rows(st, ag)
                                : g.rowc == 3 ? c3::launch_rowd(st, ag)
                                              : c3::launch_rowc(st, ag, g.rowc == 2));
                     else

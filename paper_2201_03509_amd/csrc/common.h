@@ -10,6 +10,7 @@
 #define C3_ROW_NT_F32 512    // threads per block of the FFT row pass (two blocks per CU)
 #define C3_ROW_NT_F64 1024
 #define C3_ROWC_NT 512       // threads per block of the row pass compiled per length
+#define C3_ROW_OWN 4096      // rows of a length that get a launch of their own (FP32, rowl.hip)
 #define C3_ROWS_NT 256       // the same for its short rows (FP64)
 #define C3_COL_NT 64         // threads (= columns) per block of the register column passes
 #define C3_LDS_MAX 163840    // LDS bytes one workgroup may hold on gfx950
@@ -294,9 +295,11 @@ int fft_col_class(int prec_mixed, int m1);
 // register class (c3rowc::wide); a.row_lds: the longest row's
 bool rowc_supported(int mode);
 hipError_t launch_rowc(hipStream_t st, const FftArgs &a, bool wide);
+hipError_t launch_rowl(hipStream_t st, const FftArgs &a, int L);  // one row length (rowl.hip, FP32)
 hipError_t launch_rowd(hipStream_t st, const FftArgs &a);
 hipError_t launch_rows(hipStream_t st, const FftArgs &a);
 hipError_t rowc_init_attributes();
+hipError_t rowl_init_attributes();
 hipError_t rowd_init_attributes();
 hipError_t rows_init_attributes();
 // raise the dynamic LDS limit of the FFT kernels (once per process)

@@ -575,10 +575,11 @@ hipError_t fft_init_attributes() {
     set((const void *)k_row<float, 4>);
     set((const void *)k_row<double, 4>);
     const hipError_t ec = rowc_init_attributes(), ed = rowd_init_attributes(),
-                     es = rows_init_attributes();
+                     es = rows_init_attributes(), el = rowl_init_attributes();
     if (ec != hipSuccess) e = ec;
     if (ed != hipSuccess) e = ed;
     if (es != hipSuccess) e = es;
+    if (el != hipSuccess) e = el;
     done = e;
     return e;
 }
