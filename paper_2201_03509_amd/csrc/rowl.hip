@@ -2,7 +2,7 @@
 //
 // The same code as a length's case in k_rowc (rowc.hip) runs 4 to 13 % faster as
 // a kernel of its own (the 9.4e8-sample 70 GHz-like set, rows of 2430 to 4096
-// points: 6.74 ms of row pass in the kernels of a register class, 5.94 so), but
+// points: 6.74 ms of row pass in the kernels of a register class, 6.02 so), but
 // its launch costs a tail of one block's time, 15 us: from C3_ROW_OWN rows of a
 // length on, 170 us of work, it gets its own launch.  On 1e8 samples, 700 rows a
 // length, own launches took 907 us and the shared ones 754.
