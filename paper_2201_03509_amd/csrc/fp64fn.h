@@ -110,12 +110,13 @@ __device__ __forceinline__ double sqrt_t(double x) {
     return fma(fma(-g, g, x), h, g);
 }
 
-// 1 / x for x >= 1 (0 at infinity)
+// 1 / x for x >= 1 to DBL_MAX / 4, beyond which it is subnormal (0 at infinity
+// alone; NaN stays NaN): Newton's iteration y (2 - x y) from the hardware's estimate
 __device__ __forceinline__ double rcp_t(double x) {
     double y = __builtin_amdgcn_rcp(x);
     y = fma(fma(-x, y, 1.0), y, y);
     y = fma(fma(-x, y, 1.0), y, y);
-    return x < 1e300 ? y : 0.0;
+    return x == (double)INFINITY ? 0.0 : y;
 }
 
 }  // namespace c3d

@@ -186,8 +186,11 @@ __device__ __forceinline__ cx<float> filt_row(const ModeCtx &mc, const FastCtx<f
 __device__ __forceinline__ cx<double> filt_row(const ModeCtx &mc, const FastCtx<double> &fc, int64_t k,
                                                cx<double> E, int which) {
     const double sq = k > 0 ? sqrt_q(fc, k) : 0.0, q = sq * sq;
-    const double i1q = c3d::rcp_t(1.0 + q);
-    const double h = which == 0 ? q * fc.is2 : (which == 1 ? fc.s0 * fc.s0 * i1q : q * fc.is2 * i1q);
+    // 4 / (1 + q): the quarter of 1 + q has a normal reciprocal up to the largest q
+    const double i1q = c3d::rcp_t(fma(q, 0.25, 0.25));
+    const double h = which == 0   ? q * fc.is2
+                     : which == 1 ? fc.s0 * fc.s0 * (0.25 * i1q)
+                                  : 0.25 * q * i1q * fc.is2;
     return cscale(E, mc.invsqrtN * h);
 }
 __device__ __forceinline__ cx<float> x0_row(const ModeCtx &mc, const FastCtx<float> &, int64_t k, cx<float> E) {
