@@ -7,8 +7,9 @@
 // Table-driven forms as in Tang, ACM TOMS 15 (1989) and 16 (1990): the
 // argument is split into a table point and a small rest, on which a Taylor
 // polynomial is exact to below 2^-54 of the result.  Largest errors, in units
-// of 2^-53 of the result over 10^7 arguments each: log_t 2.2, exp_t 1.0 for
-// |x| < 40, sqrt_t 1.0, rcp_t 1.0; cis_t, absolute, 1.0.  Against 80-bit
+// of 2^-53 of the result over 10^7 arguments each: log_t of an integer 1.0, of
+// the draws' uniform numbers 1.9, exp_t 1.0 for |x| < 40, sqrt_t 1.0, rcp_t 1.0;
+// cis_t, absolute, 1.0.  Against 80-bit
 // references n_corr is 3.9e-16 off and the chi^2 gradients 4e-14, as they were
 // with the library.
 #pragma once
@@ -28,15 +29,33 @@ constexpr int kLog = 0, kCis = 64, kExp = 192, kTab = 224;
 // result's terms do not cancel around m = 1: there c = 1 exactly.
 constexpr int kHalf = 27;
 
-// entry i of the tables (host); 1/c_i is rounded first and ln c_i taken of it
+// 1/c_i of the logarithm's table: any number near 1/m will do, and of 65 of them 2^-40
+// apart it is the one whose ln c_i is closest to a double (Gal and Bachelis, ACM TOMS 17
+// (1991)), so that the tabled logarithm has no error of its own.  c = 1 where the
+// result's terms would cancel.
+struct LogTab {
+    double inv[64];
+    LogTab() {
+        for (int i = 0; i < 64; ++i) {
+            const long double m = 1.0L + (i + 0.5L) / 64;
+            inv[i] = i == 0 ? 1.0 : 0.5;
+            long double off = 1.0L;
+            for (int j = -32; j <= 32 && i != 0 && i != 63; ++j) {
+                const double v = (double)(1.0L / m) * (1 + j * 0x1p-40);
+                const long double l = ln(i, v);
+                if (fabsl(l - (double)l) < off) off = fabsl(l - (double)l), inv[i] = v;
+            }
+        }
+    }
+    // x = 2^(e + 1) (m/2): ln x = (e + 1) ln 2 + ln(m inv) - ln(2 inv)
+    static long double ln(int i, double v) { return -logl(i >= kHalf ? 2.0L * v : (long double)v); }
+};
+
+// the tables' entries in order (host)
 template <typename F>
 inline void table(F &&put) {
-    for (int i = 0; i < 64; ++i) {
-        const long double m = 1.0L + (i + 0.5L) / 64;
-        const double inv = i == 0 ? 1.0 : i == 63 ? 0.5 : (double)(1.0L / m);
-        // x = 2^(e + 1) (m/2): ln x = (e + 1) ln 2 + ln(m inv) - ln(2 inv)
-        put((long double)inv, -logl(i >= kHalf ? 2.0L * inv : (long double)inv));
-    }
+    static const LogTab t;
+    for (int i = 0; i < 64; ++i) put((long double)t.inv[i], LogTab::ln(i, t.inv[i]));
     for (int i = 0; i < 128; ++i) {
         const long double a = 3.14159265358979323846264338327950288L * i / 64;
         put(i % 128 == 32 || i == 96 ? 0.0L : cosl(a), i % 64 == 0 ? 0.0L : sinl(a));
@@ -49,6 +68,7 @@ inline void table(F &&put) {
 
 // ln(2^sh x) for normal x > 0 (no zero, infinity or NaN: the callers' are
 // k + 0 >= 1 and w + 1/2)
+template <bool Comp = true>
 __device__ __forceinline__ double log_t(const cx<double> *tab, double x, int sh) {
     const uint64_t b = __double_as_longlong(x);
     const uint32_t hi = (uint32_t)(b >> 32);
@@ -66,12 +86,19 @@ __device__ __forceinline__ double log_t(const cx<double> *tab, double x, int sh)
     // ln 2 in two parts, the first with 42 significant bits: e times one rounded
     // constant would bias every logarithm of an octave by the same amount
     p = fma((double)e, 5.497923018708371e-14, fma(r * r, p, r));
-    return fma((double)e, 0.6931471805598903, t.y) + p;
+    const double s = fma((double)e, 0.6931471805598903, t.y);
+    if constexpr (!Comp) return s + p;
+    // The sum's rounding error (Fast2Sum: e ln 2 >= ln c unless e = 0) counts: q's
+    // exponent has alpha times the logarithm's error.  Without it q was 7.2 units of
+    // 2^-53 off (rms over the draws' alpha, f_knee and k), with it and with the library 5.5.
+    const double ds = fma((double)e, 0.6931471805598903, -s) + t.y;
+    return s + (p + ds);
 }
 
-// e^x (0 and infinity beyond the range; x is not NaN)
+// e^x, x held to +-Lim (of 800: 0 and infinity); NaN stays NaN
+template <int Lim = 800>
 __device__ __forceinline__ double exp_t(const cx<double> *tab, double x) {
-    x = x < -800.0 ? -800.0 : (x > 800.0 ? 800.0 : x);
+    x = x < -Lim ? -Lim : (x > Lim ? Lim : x);
     const double n = __builtin_rint(x * 46.16624130844683);  // 32 / ln 2
     const int j = (int)n;
     // ln 2 / 32 in two parts, the first with 32 significant bits: n times it is exact
@@ -100,7 +127,9 @@ __device__ __forceinline__ cx<double> cis_t(const cx<double> *tab, uint32_t w) {
     return {t.x + fma(t.x, c, -(t.y * s)), t.y + fma(t.y, c, t.x * s)};
 }
 
-// square root of a normal x > 0 far from the ends of the range
+// square root of a normal x > 0 far from the ends of the range: the coupled
+// iteration for sqrt(x) and 1 / (2 sqrt(x)) (Goldschmidt) from the hardware's estimate of
+// 1 / sqrt(x), and one residual step
 __device__ __forceinline__ double sqrt_t(double x) {
     const double y = __builtin_amdgcn_rsq(x);
     double g = x * y, h = 0.5 * y;
@@ -108,6 +137,16 @@ __device__ __forceinline__ double sqrt_t(double x) {
     g = fma(g, e, g);
     h = fma(h, e, h);
     return fma(fma(-g, g, x), h, g);
+}
+
+// q = k^malpha e^(malpha lbase), k >= 1: one exponential (the square of its half has
+// twice that one's error).  Lim = kRoot holds q to 1e-289 ... 1e289, where sqrt_t takes
+// it: sqrt(q) / (1 + q) and (w1 + sqrt(q) w2) / (1 + q) are then within 1e-144 of their
+// limits.
+constexpr int kRoot = 667;
+template <int Lim = 800>
+__device__ __forceinline__ double pow_t(const cx<double> *tab, uint32_t k, double malpha, double lbase) {
+    return exp_t<Lim>(tab, malpha * (log_t(tab, (double)k, 0) + lbase));
 }
 
 // 1 / x for x >= 1 to DBL_MAX / 4, beyond which it is subnormal (0 at infinity

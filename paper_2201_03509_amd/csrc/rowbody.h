@@ -125,35 +125,38 @@ __device__ __forceinline__ cx<float> cr_fast(const ModeCtx &mc, const FastCtx<fl
 }
 
 // The same in FP64 with the table functions of fp64fn.h: W1 = sqrt(-ln u0)
-// (cos 2 pi u1, sin 2 pi u1), W2 likewise, sqrt(q) = e^(-alpha/2 ln(f_k/f_knee)).
+// (cos 2 pi u1, sin 2 pi u1), W2 likewise.
 template <>
 struct FastCtx<double> {
     const cx<double> *tab;  // the block's tables in LDS
     double s0;              // sigma0
     double isq, oscale;     // as above
-    double halpha, lbase;   // -alpha / 2, ln(fsamp / (N fknee))
+    double malpha, lbase;   // -alpha, ln(fsamp / (N fknee))
     double is2;             // 1 / sigma0^2
 };
 
-// sqrt(q_k), k >= 1
-__device__ __forceinline__ double sqrt_q(const FastCtx<double> &fc, int64_t k) {
-    return c3d::exp_t(fc.tab, fc.halpha * (c3d::log_t(fc.tab, (double)(uint32_t)k, 0) + fc.lbase));
+// q_k (q_0 = 0), and its square root where that is drawn with (Lim = kRoot)
+template <int Lim>
+__device__ __forceinline__ double q_row(const FastCtx<double> &fc, int64_t k) {
+    return k > 0 ? c3d::pow_t<Lim>(fc.tab, (uint32_t)k, fc.malpha, fc.lbase) : 0.0;
 }
+__device__ __forceinline__ double root_row(double q, int64_t k) { return k > 0 ? c3d::sqrt_t(q) : 0.0; }
 // the draw (wa, wb) of a complex mode: sqrt(-ln u) (cos 2 pi v, sin 2 pi v)
 __device__ __forceinline__ cx<double> draw_pair(const FastCtx<double> &fc, uint32_t wa, uint32_t wb) {
-    const double r = c3d::sqrt_t(-c3d::log_t(fc.tab, (double)wa + 0.5, -32));
+    const double r = c3d::sqrt_t(-c3d::log_t<false>(fc.tab, (double)wa + 0.5, -32));
     const cx<double> c = c3d::cis_t(fc.tab, wb);
     return {r * c.x, r * c.y};
 }
 
 __device__ __forceinline__ cx<double> cr_fast(const ModeCtx &mc, const FastCtx<double> &fc, uint32_t k,
                                               cx<double> E) {
-    const double sq = sqrt_q(fc, k);
-    const double inv = c3d::rcp_t(fma(sq, sq, 1.0)) * fc.oscale;
+    const double q = c3d::pow_t<c3d::kRoot>(fc.tab, k, fc.malpha, fc.lbase);
+    const double inv = c3d::rcp_t(1.0 + q) * fc.oscale;
     cx<double> out = {E.x * fc.isq, E.y * fc.isq};
     if (!mc.mean_only) {
         const uint4 w = philox4x32_10(make_uint4(k, mc.it_lo, mc.it_hi, mc.seed_hi), mc.key);
         const cx<double> W1 = draw_pair(fc, w.x, w.y), W2 = draw_pair(fc, w.z, w.w);
+        const double sq = c3d::sqrt_t(q);
         out.x = fma(fc.s0, fma(sq, W2.x, W1.x), out.x);
         out.y = fma(fc.s0, fma(sq, W2.y, W1.y), out.y);
     }
@@ -167,14 +170,14 @@ __device__ __forceinline__ cx<float> cr_real(const ModeCtx &mc, const FastCtx<fl
 }
 __device__ __forceinline__ cx<double> cr_real(const ModeCtx &mc, const FastCtx<double> &fc, int64_t k,
                                               cx<double> E) {
-    const double sq = k > 0 ? sqrt_q(fc, k) : 0.0;
+    const double q = q_row<c3d::kRoot>(fc, k);
     double v = E.x * mc.invsqrtN;
     if (!mc.mean_only) {
         const uint4 w = philox4x32_10(make_uint4((uint32_t)k, mc.it_lo, mc.it_hi, mc.seed_hi), mc.key);
         const double W1 = draw_pair(fc, w.x, w.y).x, W2 = draw_pair(fc, w.z, w.w).x;
-        v = fma(fc.s0 * 1.41421356237309504880, fma(sq, W2, W1), v);
+        v = fma(fc.s0 * 1.41421356237309504880, fma(root_row(q, k), W2, W1), v);
     }
-    return {v * c3d::rcp_t(fma(sq, sq, 1.0)), 0.0};
+    return {v * c3d::rcp_t(1.0 + q), 0.0};
 }
 
 // filt_mode, x0_mode and whittle_mode (fftmode.h): as they are in FP32, on the
@@ -185,7 +188,7 @@ __device__ __forceinline__ cx<float> filt_row(const ModeCtx &mc, const FastCtx<f
 }
 __device__ __forceinline__ cx<double> filt_row(const ModeCtx &mc, const FastCtx<double> &fc, int64_t k,
                                                cx<double> E, int which) {
-    const double sq = k > 0 ? sqrt_q(fc, k) : 0.0, q = sq * sq;
+    const double q = q_row<800>(fc, k);
     // 4 / (1 + q): the quarter of 1 + q has a normal reciprocal up to the largest q
     const double i1q = c3d::rcp_t(fma(q, 0.25, 0.25));
     const double h = which == 0   ? q * fc.is2
@@ -198,13 +201,12 @@ __device__ __forceinline__ cx<float> x0_row(const ModeCtx &mc, const FastCtx<flo
 }
 __device__ __forceinline__ cx<double> x0_row(const ModeCtx &mc, const FastCtx<double> &fc, int64_t k,
                                              cx<double> E) {
-    const double sq = k > 0 ? sqrt_q(fc, k) : 0.0;
-    const double i1q = c3d::rcp_t(fma(sq, sq, 1.0));
+    const double q = q_row<c3d::kRoot>(fc, k), i1q = c3d::rcp_t(1.0 + q);
     cx<double> v = cscale(E, mc.invsqrtN * (fc.s0 * fc.s0 * i1q));
     if (!mc.mean_only) {
         const uint4 w = philox4x32_10(make_uint4((uint32_t)k, mc.it_lo, mc.it_hi, mc.seed_hi), mc.key);
         const bool real = k == 0 || k == mc.M;
-        const double h = fc.s0 * i1q * sq * (real ? 1.41421356237309504880 : 1.0);
+        const double h = fc.s0 * i1q * root_row(q, k) * (real ? 1.41421356237309504880 : 1.0);
         const cx<double> W = draw_pair(fc, w.z, w.w);
         v.x = fma(h, W.x, v.x);
         if (!real) v.y = fma(h, W.y, v.y);
@@ -232,7 +234,7 @@ __device__ __forceinline__ FastCtx<T> fast_ctx(const ModeCtx &mc, const cx<T> *t
         fc.s0 = mc.sigma0;
         fc.isq = 0.5 * mc.invsqrtN;
         fc.oscale = 0.5 * mc.outscale;
-        fc.halpha = 0.5 * mc.malpha;
+        fc.malpha = mc.malpha;
         fc.lbase = mc.lbase;
         fc.is2 = 1.0 / (mc.sigma0 * mc.sigma0);
     } else {
