@@ -220,10 +220,10 @@ __device__ __forceinline__ void whittle_row(const ModeCtx &mc, const FastCtx<flo
 __device__ __forceinline__ void whittle_row(const ModeCtx &mc, const FastCtx<double> &fc, int64_t k, cx<double> E,
                                             Wsum &s) {
     const double lr = c3d::log_t(fc.tab, (double)(uint32_t)k, 0) + fc.lbase;
-    const double ip = 1.0 - (E.x * E.x + E.y * E.y) * mc.iscale * c3d::exp_t(fc.tab, mc.malpha * lr);
-    s.a += (1.0 - ip) + (mc.l2s0 - mc.malpha * lr);
-    s.b += ip;
-    s.c = fma(ip, lr, s.c);
+    const double ip = (E.x * E.x + E.y * E.y) * mc.iscale * c3d::exp_t(fc.tab, mc.malpha * lr);
+    s.a += ip + (mc.l2s0 - mc.malpha * lr);
+    s.b += 1.0 - ip;
+    s.c = fma(1.0 - ip, lr, s.c);
 }
 
 template <typename T>
