@@ -151,8 +151,8 @@ struct tod_ctx_s {
     // masked n_corr solver: Krylov vectors and the transform output (the
     // precision's type), partial sums, per-segment state, active flags and the
     // active-segment count
-    DevBuf cg_x, cg_res, cg_fin, cg_fout, cg_part, cg_state, cg_act, cg_has_gap;
-    DevBuf cg_cnt, cg_base, cg_gap_idx, cg_y, cg_rho, cg_p, cg_gap_tiles, cg_seg_gap_tiles;
+    DevBuf cg_x, cg_res, cg_fin, cg_fout, cg_part, cg_gpart, cg_state, cg_act, cg_has_gap;
+    DevBuf cg_cnt, cg_base, cg_gap_idx, cg_y, cg_rho, cg_p, cg_gap_tiles, cg_seg_gap_tiles, cg_groups, cg_seg_groups;
     // gain draw: filtered template and data (per sample), per-tile partial sums
     DevBuf gain_kt, gain_kd, gain_part;
     // noise-parameter draw: periodogram bins per segment, white-residual partials
@@ -1318,6 +1318,13 @@ static tod_status cg_tiles(tod_ctx ctx, Plan *P) {
     return TOD_OK;
 }
 
+// Gap tiles of a segment up to which every wave adds up their sums by itself; beyond,
+// two launches more an iteration add them in groups first (k_gap_sum).  Us an
+// iteration by itself and in groups: 16 segments of 292 tiles 162 and 163, one
+// 57 and 59; 8 of 585 tiles 195 and 183, one 87.4 and 86.7; one of 2441 tiles 181 and
+// 133, of 19531 tiles 3826 and 1587.
+constexpr int kGapDirect = 400;
+
 tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const void *d,
                                tod_dtype d_dtype, const void *s, const uint8_t *mask,
                                const double *sigma0, const double *fknee, const double *alpha,
@@ -1446,6 +1453,22 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
         if (t != P->ncg) return fail(ctx, TOD_EHIP, "extended tile layout mismatch");
     }
     if (gt.size() > (size_t)INT32_MAX / 2) return fail(ctx, TOD_ENOTSUP, "too many masked samples");
+    // the tiles' sums in groups first, where a segment has many tiles
+    std::vector<int4> groups;
+    std::vector<int2> seg_gr(nseg, make_int2(0, 0));
+    int most = 0;
+    for (const int2 &x : seg_gt) most = std::max(most, x.y);
+    if (most > kGapDirect) {
+        for (int sgi = 0; sgi < nseg; ++sgi) {
+            seg_gr[sgi].x = (int)groups.size();
+            for (int o = 0; o < seg_gt[sgi].y; o += C3_GAP_GROUP)
+                groups.push_back(make_int4(sgi, seg_gt[sgi].x + o, std::min(C3_GAP_GROUP, seg_gt[sgi].y - o), 0));
+            seg_gr[sgi].y = (int)groups.size() - seg_gr[sgi].x;
+        }
+        HIPCHK(ctx->cg_gpart.ensure(2 * groups.size() * 8 + 64));
+        HIPCHK(ctx->cg_groups.upload(groups, st));
+        HIPCHK(ctx->cg_seg_groups.upload(seg_gr, st));
+    }
     HIPCHK(ctx->cg_gap_idx.ensure((size_t)total * 8 + 64));
     HIPCHK(ctx->cg_y.ensure((size_t)total * 8 + 64));
     HIPCHK(ctx->cg_rho.ensure((size_t)total * 8 + 64));
@@ -1469,6 +1492,10 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     gv.rho = (double *)ctx->cg_rho.p;
     gv.p = (double *)ctx->cg_p.p;
     gv.seg_tiles = (const int2 *)ctx->cg_seg_gap_tiles.p;
+    gv.groups = (const int4 *)ctx->cg_groups.p;
+    gv.ngroup = (int)groups.size();
+    gv.seg_groups = (const int2 *)ctx->cg_seg_groups.p;
+    gv.gpart = (double *)ctx->cg_gpart.p;
     gv.tol2 = tol2;
     gv.max_iter = max_iter;
     HIPCHK(hipHostGetDevicePointer((void **)&gv.go_on, ctx->h_go_on, 0));
@@ -1492,7 +1519,9 @@ tod_status sample_ncorr_masked(tod_ctx ctx, const tod_layout *lay, tod_prec prec
         if ((r = run_fft(ctx, st, P, mixed, a, 3)) != TOD_OK) return r;  // M S p
         gv.it = it;
         HIPCHK(vec(c3::CG_OP_GAP_PQ, gv));
+        if (gv.ngroup) HIPCHK(vec(c3::CG_OP_GAP_SUM_PQ, gv));
         HIPCHK(vec(c3::CG_OP_GAP_UPDATE, gv));
+        if (gv.ngroup) HIPCHK(vec(c3::CG_OP_GAP_SUM_RR, gv));
         HIPCHK(vec(c3::CG_OP_GAP_DIR, gv));
         HIPCHK(hipEventRecord(ctx->cg_ev[it & 1], st));
         if (it > 1) {

@@ -338,6 +338,7 @@ hipError_t launch_set_u64(hipStream_t st, uint64_t *p, uint64_t a, uint64_t b);
 // ---- masked n_corr draw (gapfill.hip): per-segment CG state and vector passes
 #define C3_CG_TILE 4096      // extended reals per elementwise tile
 #define C3_GAP_TILE 1024     // entries of the gap list per tile: four a thread
+#define C3_GAP_GROUP 64      // tiles whose partial sums one wave adds where a segment has many
 struct CgState {
     double bb;       // rho_0 . rho_0: the stopping rule's reference
     double rr[2];    // rho . rho after iteration it in rr[it & 1]
@@ -353,6 +354,8 @@ enum CgOp {
     CG_OP_GAP_PQ,       // partial p.q, q = sigma0^2 p - fout[gap]    (gap tiles)
     CG_OP_GAP_UPDATE,   // y += alpha p, rho -= alpha q, partial rho.rho (gap tiles)
     CG_OP_GAP_DIR,      // p = rho + beta p, fin[gap] = p, stopping rule (gap tiles)
+    CG_OP_GAP_SUM_PQ,   // partial sums of the groups                 (groups of gap tiles)
+    CG_OP_GAP_SUM_RR,
     CG_OP_CROP          // out = (x0 + fout)[0:n]                     (sample tiles)
 };
 #define C3_CG_SLOTS 4               // flags of iterations to come, used in turn
@@ -364,6 +367,10 @@ struct CgVecArgs {
     int32_t *act;               // per segment: still iterating
     CgState *cs;
     const int2 *seg_tiles;      // gap tiles of each segment (first, number)
+    const int4 *groups;         // groups of gap tiles (seg, first tile, number, 0)
+    int ngroup;                 // 0: sums straight over the tiles
+    const int2 *seg_groups;     // groups of each segment (first, number)
+    double *gpart;              // per-group partial sums: of p.q, then of rho.rho
     int it;                     // iteration, from 1
     double tol2;                // DIR: stopping rule
     int max_iter;

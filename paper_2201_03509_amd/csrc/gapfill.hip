@@ -195,7 +195,24 @@ __global__ __launch_bounds__(C3_NT) void k_gap_scatter(const int4 *__restrict__ 
 // 17 as three (32 segments of 27000 masked positions).  One block per segment for
 // all of it took 46: a single CU moves the 3 MB no faster.
 
-// sum of a segment's tile partials, the same in every lane
+// Every wave adding up every tile of its segment is quadratic in a segment's masked
+// positions: where a segment has many tiles (api.cpp says from how many on), a launch
+// of one wave per C3_GAP_GROUP tiles adds these up first, and the waves add the groups.
+__global__ __launch_bounds__(C3_NT) void k_gap_sum(const int4 *__restrict__ groups, int ngroup,
+                                                   const int32_t *__restrict__ act, const double *__restrict__ part,
+                                                   double *__restrict__ gpart) {
+    const int q = blockIdx.x * (C3_NT / 64) + (threadIdx.x >> 6);
+    if (q >= ngroup) return;
+    const int4 g = groups[q];
+    if (!act[g.x]) return;
+    const int i = threadIdx.x & 63;
+    double v = i < g.z ? part[g.y + i] : 0.0;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_down(v, o, 64);
+    if (i == 0) gpart[q] = v;
+}
+
+// sum of a segment's partials (of its tiles or their groups), the same in every lane
 __device__ __forceinline__ double seg_total(const double *__restrict__ part, int2 tr) {
     double v = 0;
     for (int i = threadIdx.x & 63; i < tr.y; i += 64) v += part[tr.x + i];
@@ -235,7 +252,7 @@ __global__ __launch_bounds__(C3_NT) void k_gap_pq(const int4 *__restrict__ gtile
 template <typename T>
 __global__ __launch_bounds__(C3_NT) void k_gap_update(const int4 *__restrict__ gtiles, const int32_t *__restrict__ act,
                                                       const CgState *__restrict__ cs,
-                                                      const int2 *__restrict__ seg_tiles, int it,
+                                                      const int2 *__restrict__ seg_sums, int it,
                                                       const int64_t *__restrict__ gap_idx,
                                                       const double *__restrict__ sigma0, const double *__restrict__ p,
                                                       const T *__restrict__ fout, double *__restrict__ y,
@@ -256,7 +273,7 @@ __global__ __launch_bounds__(C3_NT) void k_gap_update(const int4 *__restrict__ g
         rv[u] = rho[j];
         f[u] = fout[gap_idx[j]];
     }
-    const double pq = seg_total(part_pq, seg_tiles[tl.x]);
+    const double pq = seg_total(part_pq, seg_sums[tl.x]);
     if (!(pq > 0.0)) return;  // breakdown (the small system is positive definite): DIR stops the segment
     const double al = cs[tl.x].rr[(it - 1) & 1] / pq;
     double acc = 0;
@@ -278,7 +295,8 @@ __global__ __launch_bounds__(C3_NT) void k_gap_update(const int4 *__restrict__ g
 // each block finds stopped by itself.
 template <typename T>
 __global__ __launch_bounds__(C3_NT) void k_gap_dir(const int4 *__restrict__ gtiles, int32_t *act, CgState *cs,
-                                                   const int2 *__restrict__ seg_tiles, int it, double tol2,
+                                                   const int2 *__restrict__ seg_tiles,
+                                                   const int2 *__restrict__ seg_sums, int it, double tol2,
                                                    int max_iter, int32_t *__restrict__ go_on,
                                                    const int64_t *__restrict__ gap_idx,
                                                    const double *__restrict__ rho, double *__restrict__ p,
@@ -297,8 +315,8 @@ __global__ __launch_bounds__(C3_NT) void k_gap_dir(const int4 *__restrict__ gtil
         rv[u] = rho[j];
         g[u] = gap_idx[j];
     }
-    const int2 tr = seg_tiles[tl.x];
-    const bool first = (int)blockIdx.x == tr.x && threadIdx.x == 0;
+    const int2 tr = seg_sums[tl.x];
+    const bool first = (int)blockIdx.x == seg_tiles[tl.x].x && threadIdx.x == 0;
     CgState *c = cs + tl.x;
     if (!(seg_total(part_pq, tr) > 0.0)) {
         if (first) act[tl.x] = 0;
@@ -386,7 +404,13 @@ namespace c3 {
 hipError_t launch_cg_vec(hipStream_t st, int mixed, int op, const CgVecArgs &a) {
     if (a.ntile <= 0) return hipSuccess;
     if (op == CG_OP_INIT && a.s_f64 != (mixed ? 0 : 1)) return hipErrorInvalidValue;  // s: the precision's type
+    if ((op == CG_OP_GAP_SUM_PQ || op == CG_OP_GAP_SUM_RR) && a.ngroup <= 0) return hipSuccess;
     const dim3 g((unsigned)a.ntile), b(C3_NT);
+    const dim3 gs((unsigned)((a.ngroup + C3_NT / 64 - 1) / (C3_NT / 64)));
+    // what UPDATE and DIR add up of p.q and rho.rho
+    const int2 *seg_sums = a.ngroup > 0 ? a.seg_groups : a.seg_tiles;
+    const double *sums = a.ngroup > 0 ? a.gpart : a.part;
+    const int nsum = a.ngroup > 0 ? a.ngroup : a.ntile;
 #define C3_CG_OPS(T)                                                                                          \
     switch (op) {                                                                                             \
     case CG_OP_INIT:                                                                                          \
@@ -414,12 +438,20 @@ hipError_t launch_cg_vec(hipStream_t st, int mixed, int op, const CgVecArgs &a) 
                            (const T *)a.fout, a.part);                                                        \
         break;                                                                                                \
     case CG_OP_GAP_UPDATE:                                                                                    \
-        hipLaunchKernelGGL(k_gap_update<T>, g, b, 0, st, a.tiles, a.act, a.cs, a.seg_tiles, a.it, a.gap_idx,  \
-                           a.sigma0, a.p, (const T *)a.fout, a.y, a.rho, a.part, a.part + a.ntile);           \
+        hipLaunchKernelGGL(k_gap_update<T>, g, b, 0, st, a.tiles, a.act, a.cs, seg_sums, a.it, a.gap_idx,     \
+                           a.sigma0, a.p, (const T *)a.fout, a.y, a.rho, sums, a.part + a.ntile);             \
         break;                                                                                                \
     case CG_OP_GAP_DIR:                                                                                       \
-        hipLaunchKernelGGL(k_gap_dir<T>, g, b, 0, st, a.tiles, a.act, a.cs, a.seg_tiles, a.it, a.tol2,        \
-                           a.max_iter, a.go_on, a.gap_idx, a.rho, a.p, a.part, a.part + a.ntile, (T *)a.fin); \
+        hipLaunchKernelGGL(k_gap_dir<T>, g, b, 0, st, a.tiles, a.act, a.cs, a.seg_tiles, seg_sums, a.it,      \
+                           a.tol2, a.max_iter, a.go_on, a.gap_idx, a.rho, a.p, sums, sums + nsum,             \
+                           (T *)a.fin);                                                                       \
+        break;                                                                                                \
+    case CG_OP_GAP_SUM_PQ:                                                                                    \
+        hipLaunchKernelGGL(k_gap_sum, gs, b, 0, st, a.groups, a.ngroup, a.act, a.part, a.gpart);              \
+        break;                                                                                                \
+    case CG_OP_GAP_SUM_RR:                                                                                    \
+        hipLaunchKernelGGL(k_gap_sum, gs, b, 0, st, a.groups, a.ngroup, a.act, a.part + a.ntile,              \
+                           a.gpart + a.ngroup);                                                               \
         break;                                                                                                \
     case CG_OP_CROP:                                                                                          \
         hipLaunchKernelGGL(k_cg_crop<T>, g, b, 0, st, a.tiles, a.segs, a.has_gap, (const T *)a.x,             \
