@@ -1088,7 +1088,7 @@ tod_status tod_ctx_create(tod_ctx *out, int device, void *hip_stream) {
         delete ctx;
         return TOD_EHIP;
     }
-    if (c3::fft_init_attributes() != hipSuccess) {
+    if (c3::fft_init_attributes() != hipSuccess || c3::dec_init_attributes() != hipSuccess) {
         delete ctx;
         return TOD_EHIP;
     }

@@ -302,8 +302,10 @@ hipError_t rowc_init_attributes();
 hipError_t rowl_init_attributes();
 hipError_t rowd_init_attributes();
 hipError_t rows_init_attributes();
-// raise the dynamic LDS limit of the FFT kernels (once per process)
+// raise the dynamic LDS limit of the FFT kernels, of the decoders (once per device, for
+// the current one)
 hipError_t fft_init_attributes();
+hipError_t dec_init_attributes();
 
 // tiles and runs: the binning runs (get_bin_runs); err receives C3_ERR_NONFINITE
 hipError_t launch_bin_tiles(hipStream_t st, const LayoutDev &L, int mixed, const int4 *tiles,

@@ -26,6 +26,7 @@
 #include <type_traits>
 
 #include "common.h"
+#include "perdev.h"
 
 namespace {
 
@@ -1152,21 +1153,6 @@ namespace {
 bool staged_words(int64_t words, int64_t nchunk, uint32_t room) {
     return nchunk > 0 && (double)words / (double)nchunk * C3_DEC_NT * 1.05 + 2 * kWordsPer <= (double)room;
 }
-hipError_t dec_attributes() {
-    static const hipError_t done = [] {
-        hipError_t e = hipSuccess;
-        auto set = [&](const void *f) {
-            const hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, C3_LDS_MAX - 4096);
-            if (r != hipSuccess) e = r;
-        };
-        set((const void *)k_decode32);
-        set((const void *)k_decode32_1<0>);
-        set((const void *)k_decode32_1<1>);
-        set((const void *)k_decode32_1<2>);
-        return e;
-    }();
-    return done;
-}
 
 template <int KIND>
 void launch_decode1(hipStream_t st, const LayoutDev &L, const HuffDev &h, DecTab *tabs, const DecodeTask *tasks,
@@ -1187,11 +1173,24 @@ hipError_t launch_decode_stream(hipStream_t st, const LayoutDev &L, const HuffDe
                                 const DecodeTask *tasks, int ntask, int kind, double quantum,
                                 uint32_t flag_mask, void *out, uint8_t *mask_out, uint32_t *err) {
     if (ntask <= 0) return hipSuccess;
-    const hipError_t e = dec_attributes();
-    if (e != hipSuccess) return e;
     auto *go = kind == 0 ? launch_decode1<0> : kind == 1 ? launch_decode1<1> : launch_decode1<2>;
     go(st, L, h, tabs, tasks, ntask, quantum, flag_mask, out, mask_out, err);
     return hipGetLastError();
+}
+
+hipError_t dec_init_attributes() {
+    static PerDevice inits;
+    int dev = -1;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
+    return inits.once<hipError_t>(dev, [&] {
+        for (const void *f : {(const void *)k_decode32, (const void *)k_decode32_1<0>, (const void *)k_decode32_1<1>,
+                              (const void *)k_decode32_1<2>}) {
+            const hipError_t r = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, C3_LDS_MAX - 4096);
+            if (r != hipSuccess) e = r;
+        }
+        return e;
+    });
 }
 
 hipError_t noalloc_scratch(void **ptr) {
@@ -1227,8 +1226,6 @@ hipError_t launch_decode(hipStream_t st, const LayoutDev &L, const HuffDev &hp, 
                          DecTab *tabs, const DecodeTask *tasks, int ntask, int32_t *pix_out,
                          uint16_t *psi_out, uint32_t *err) {
     if (ntask <= 0) return hipSuccess;
-    const hipError_t e = dec_attributes();
-    if (e != hipSuccess) return e;
     const dim3 g(ntask), b(C3_DEC_NT);
     hipLaunchKernelGGL(k_tables, dim3(hp.ntable + hs.ntable), dim3(1024), 0, st, hp, hs, tabs);
     if (hp.chunk_len == 32 && staged_words(hp.nwords + hs.nwords, hp.nchunk, kPairWords))

@@ -19,6 +19,7 @@
 #include "common.h"
 #include "fftdev.h"
 #include "fftmode.h"
+#include "perdev.h"
 #include "rng.h"
 
 namespace {
@@ -549,9 +550,7 @@ __global__ __launch_bounds__(row_nt<T>()) void k_row(FftArgs a) {
 
 namespace c3 {
 
-hipError_t fft_init_attributes() {
-    static hipError_t done = hipErrorNotReady;
-    if (done == hipSuccess) return done;
+static hipError_t init_attributes() {
     // room for the kernels' static arrays (reduction sums, periodogram bins: under
     // 2 KB); the largest dynamic request (two rows of 5040 FP32 points) is 80 KB
     const int lim = C3_LDS_MAX - 4096;
@@ -580,8 +579,14 @@ hipError_t fft_init_attributes() {
     if (ed != hipSuccess) e = ed;
     if (es != hipSuccess) e = es;
     if (el != hipSuccess) e = el;
-    done = e;
     return e;
+}
+
+hipError_t fft_init_attributes() {
+    static PerDevice inits;
+    int dev = -1;
+    const hipError_t e = hipGetDevice(&dev);
+    return e != hipSuccess ? e : inits.once<hipError_t>(dev, init_attributes);
 }
 
 hipError_t launch_fft_pass(hipStream_t st, int mixed, const FftArgs &a, int pass) {
