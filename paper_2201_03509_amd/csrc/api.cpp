@@ -517,19 +517,25 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
         }
         // one launch per register class and blocks per CU (a launch's LDS is its
         // longest row's), longest rows first
-        std::map<std::pair<int, int>, std::pair<int, std::vector<RowTask>>> launches;
+        std::map<std::pair<int, int>, std::vector<int>> lengths;  // (class, blocks per CU) -> row lengths
+        // FP64: the mode tables behind the rows, and always two blocks (of short
+        // rows, four) to a CU
+        auto row_lds = [&](int len) { return 2 * len * esz + (mixed ? 0 : c3d::kTab * esz); };
         for (auto it = browc.rbegin(); it != browc.rend(); ++it) {
-            // FP64: the mode tables behind the rows, and always two blocks (of short
-            // rows, four) to a CU
-            const int rl = 2 * it->first * esz + (mixed ? 0 : c3d::kTab * esz);
             const int cls = !mixed ? (c3rowc::short_row(it->first) ? 4 : 3) : c3rowc::wide(it->first) ? 2 : 1;
-            if (mixed && it->second.size() >= C3_ROW_OWN) {  // a launch of its own: see rowl.hip
-                launches[{it->first, 0}] = {rl, it->second};
-                continue;
+            lengths[{cls, std::min(mixed ? 3 : 2, C3_LDS_MAX / row_lds(it->first))}].push_back(it->first);
+        }
+        std::map<std::pair<int, int>, std::pair<int, std::vector<RowTask>>> launches;
+        for (const auto &kv : lengths) {
+            std::vector<int64_t> points;
+            for (int len : kv.second) points.push_back((int64_t)len * (int64_t)browc[len].size());
+            const std::vector<char> own = c3tune::own_rows(points);
+            for (size_t i = 0; i < points.size(); ++i) {
+                const int len = kv.second[i];
+                auto &g = launches[mixed && own[i] ? std::make_pair(len, 0) : kv.first];
+                g.first = std::max(g.first, row_lds(len));
+                g.second.insert(g.second.end(), browc[len].begin(), browc[len].end());
             }
-            auto &g = launches[{cls, std::min(mixed ? 3 : 2, C3_LDS_MAX / rl)}];
-            g.first = std::max(g.first, rl);
-            g.second.insert(g.second.end(), it->second.begin(), it->second.end());
         }
         for (auto &kv : launches) {
             std::vector<RowTask> &v = kv.second.second;

@@ -10,7 +10,6 @@
 #define C3_ROW_NT_F32 512    // threads per block of the FFT row pass (two blocks per CU)
 #define C3_ROW_NT_F64 1024
 #define C3_ROWC_NT 512       // threads per block of the row pass compiled per length
-#define C3_ROW_OWN 4096      // rows of a length that get a launch of their own (FP32, rowl.hip)
 #define C3_ROWS_NT 256       // the same for its short rows (FP64)
 #define C3_COL_NT 64         // threads (= columns) per block of the register column passes
 #define C3_LDS_MAX 163840    // LDS bytes one workgroup may hold on gfx950

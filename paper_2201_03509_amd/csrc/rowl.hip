@@ -3,9 +3,12 @@
 // The same code as a length's case in k_rowc (rowc.hip) runs 4 to 13 % faster as
 // a kernel of its own (the 9.4e8-sample 70 GHz-like set, rows of 2430 to 4096
 // points: 6.74 ms of row pass in the kernels of a register class, 6.02 so), but
-// its launch costs a tail of one block's time, 15 us: from C3_ROW_OWN rows of a
-// length on, 170 us of work, it gets its own launch.  On 1e8 samples, 700 rows a
-// length, own launches took 907 us and the shared ones 754.
+// a launch costs a tail of one block's time, 15 us.  c3tune::own_rows weighs the two.  Us
+// of row pass, shared and own: one length, 2000 points, 3000 tasks 87.5 and 82.7, 500
+// tasks 30.0 and 28.2; two of 3700 points, 1280 tasks each 145 and 156, 2560 tasks 284 and
+// 279; three of 2200 points, 2900 tasks 503 and 515 (a fourth beside them); six of
+// 2150 points, 3500 tasks 590 and 603; some thirty of 4000 points, 700 tasks each, 754
+// and 907.
 #include "rowc_body.h"
 
 namespace {

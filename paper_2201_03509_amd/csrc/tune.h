@@ -30,6 +30,27 @@ struct FftChoice {
     std::vector<int> r1, r2;
 };
 
+// FP32: which of the row lengths that could share a launch get one of their own
+// (rowl.hip).  points[i]: row tasks times points a row, what length i costs.  In the
+// shared launch a length takes some 6 % longer; a launch more costs a tail, as much as
+// kOwnPoints save.  So a length of that many has its own launch, and the k others
+// either share one, or have k of their own where those k - 1 tails are saved; one that is
+// left alone always does.
+constexpr int64_t kOwnPoints = 17000000;
+inline std::vector<char> own_rows(const std::vector<int64_t> &points) {
+    std::vector<char> own(points.size(), 0);
+    int64_t rest = 0, k = 0;
+    for (size_t i = 0; i < points.size(); ++i) {
+        own[i] = points[i] >= kOwnPoints;
+        if (!own[i]) {
+            rest += points[i];
+            ++k;
+        }
+    }
+    if (rest >= kOwnPoints * (k - 1)) std::fill(own.begin(), own.end(), 1);
+    return own;
+}
+
 // longest row the row pass takes: two rows in one in-place LDS buffer of at
 // most 80 KB, so that two row blocks share a CU (the stage code is sized for it)
 inline int row_cap(int mixed) { return mixed ? 5040 : 2520; }
