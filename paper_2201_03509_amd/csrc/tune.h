@@ -51,6 +51,17 @@ inline std::vector<char> own_rows(const std::vector<int64_t> &points) {
     return own;
 }
 
+// FP32 columns of the middle class (40 to 64 points): waves per SIMD of a launch of
+// `blocks` one-wave blocks.  The pass is bound by memory, so a round of three waves on each
+// of 1024 SIMDs takes half as long again as one of two, full or not: the fewer
+// wave-rounds win, and two waves, which do not spill, a tie.  Forward pass of 60
+// segments, us with three and with two: 2400 blocks 35 and 41, 3240 to 3660 blocks 64
+// and 53; 80 segments of 1.15e5 samples (2900 blocks), the gain draw whole: 272 and 282.
+inline int col_waves(int64_t blocks) {
+    const int64_t three = (blocks + 3071) / 3072 * 3, two = (blocks + 2047) / 2048 * 2;
+    return three < two ? 3 : 2;
+}
+
 // longest row the row pass takes: two rows in one in-place LDS buffer of at
 // most 80 KB, so that two row blocks share a CU (the stage code is sized for it)
 inline int row_cap(int mixed) { return mixed ? 5040 : 2520; }
