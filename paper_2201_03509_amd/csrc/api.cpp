@@ -395,7 +395,9 @@ std::vector<int4> split_tiles(const std::vector<TileWork> &v, int64_t want, int 
     return out;
 }
 
-tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key, Plan **out) {
+// may_own: FP32 row lengths that are worth it get launches of their own (c3tune::own_rows);
+// false: they all share
+tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key, Plan **out, bool may_own = true) {
     auto P = std::make_unique<Plan>();
     P->key = key;
     P->gen = ++ctx->gen_counter;
@@ -532,7 +534,7 @@ tod_status build_plan(tod_ctx ctx, const tod_layout *L, int mixed, uint64_t key,
             const std::vector<char> own = c3tune::own_rows(points);
             for (size_t i = 0; i < points.size(); ++i) {
                 const int len = kv.second[i];
-                auto &g = launches[mixed && own[i] ? std::make_pair(len, 0) : kv.first];
+                auto &g = launches[mixed && may_own && own[i] ? std::make_pair(len, 0) : kv.first];
                 g.first = std::max(g.first, row_lds(len));
                 g.second.insert(g.second.end(), browc[len].begin(), browc[len].end());
             }
@@ -2012,8 +2014,9 @@ std::string band_key(const tod_band &b) {
 }
 
 // Mean time (ms) of the three n_corr FFT passes for K segments of length M
-// with the FFT split `ch`.
-tod_status time_fft_choice(tod_ctx ctx, int mixed, int64_t M, const c3tune::FftChoice &ch, int K,
+// with the FFT split `ch`, its rows in the kernel of their length (own) or in the
+// shared one: the two differ by 4 to 13 %, more than the splits often do.
+tod_status time_fft_choice(tod_ctx ctx, int mixed, int64_t M, const c3tune::FftChoice &ch, int K, bool own,
                            float *ms_out) {
     c3tune::Table saved = ctx->tuned;
     ctx->tuned.put(mixed, M, ch);
@@ -2038,7 +2041,7 @@ tod_status time_fft_choice(tod_ctx ctx, int mixed, int64_t M, const c3tune::FftC
     L.bands = &b;
     const uint64_t key = layout_key(&L, mixed, 0x7475ull ^ ctx->tuned.version);
     Plan *P = nullptr;
-    tod_status r = build_plan(ctx, &L, mixed, key, &P);
+    tod_status r = build_plan(ctx, &L, mixed, key, &P, own);
     ctx->tuned = saved;
     if (r != TOD_OK) return r;
     r = ensure_work(ctx, P);
@@ -2117,6 +2120,8 @@ tod_status tod_autotune(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const
         const int64_t n = lay->h_seg_off[s + 1] - lay->h_seg_off[s];
         if (n > 0) count[next_5smooth(n)]++;
     }
+    // the row kernels that the layout will run
+    const std::map<int64_t, bool> own = c3tune::own_lengths(count);
     for (auto &kv : count) {
         const int64_t M = kv.first;
         c3tune::FftChoice have;
@@ -2130,8 +2135,8 @@ tod_status tod_autotune(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const
         c3tune::FftChoice bc;
         for (const c3tune::FftChoice &c : c3tune::candidates(M, mixed)) {
             float ms, ms2;
-            if ((r = time_fft_choice(ctx, mixed, M, c, K, &ms)) != TOD_OK) return r;
-            if ((r = time_fft_choice(ctx, mixed, M, c, K, &ms2)) != TOD_OK) return r;
+            if ((r = time_fft_choice(ctx, mixed, M, c, K, own.at(M), &ms)) != TOD_OK) return r;
+            if ((r = time_fft_choice(ctx, mixed, M, c, K, own.at(M), &ms2)) != TOD_OK) return r;
             ms = std::min(ms, ms2);
             if (ms < 0.97f * best) {
                 best = ms;

@@ -51,6 +51,19 @@ inline std::vector<char> own_rows(const std::vector<int64_t> &points) {
     return own;
 }
 
+// The same before the splits are known, for the tuner: count[M] segments of M complex
+// points have about M / 2 row points each, and their rows are taken to be of one
+// register class.  True: the rows of M get launches of their own.
+inline std::map<int64_t, bool> own_lengths(const std::map<int64_t, int> &count) {
+    std::vector<int64_t> points;
+    for (const auto &kv : count) points.push_back(kv.first / 2 * kv.second);
+    const std::vector<char> own = own_rows(points);
+    std::map<int64_t, bool> out;
+    size_t i = 0;
+    for (const auto &kv : count) out[kv.first] = own[i++];
+    return out;
+}
+
 // FP32 columns of the middle class (40 to 64 points): waves per SIMD of a launch of
 // `blocks` one-wave blocks.  The pass is bound by memory, so a round of three waves on each
 // of 1024 SIMDs takes half as long again as one of two, full or not: the fewer

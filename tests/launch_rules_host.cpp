@@ -31,6 +31,13 @@ int main() {
     EXPECT((own_rows({P - 1, P - 1, 1}) == V{0, 0, 0}));
     EXPECT((own_rows({P - 1, P - 1, 2}) == V{1, 1, 1}));
     EXPECT((own_rows({P, P, P, P}) == V{1, 1, 1, 1}));
+    // what the tuner times: three lengths of two segments share, one length does not, nor
+    // does one with many segments beside others
+    const auto few = c3tune::own_lengths({{100000, 2}, {112500, 2}, {115200, 2}});
+    for (const auto &kv : few) EXPECT(!kv.second);
+    EXPECT(c3tune::own_lengths({{100000, 2}}).at(100000));
+    const auto big = c3tune::own_lengths({{100000, (int)(P / 50000)}, {112500, 2}, {115200, 2}});
+    EXPECT(big.at(100000) && !big.at(112500) && !big.at(115200));
     for (int64_t n : {1, 2048, 3073, 4096, 6145, 8192}) EXPECT(col_waves(n) == 2);
     for (int64_t n : {2049, 3072}) EXPECT(col_waves(n) == 3);
     EXPECT(col_waves(4097) == 2 && col_waves(6144) == 2);  // a tie: six wave-rounds either way
