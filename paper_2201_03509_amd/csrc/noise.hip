@@ -195,8 +195,8 @@ __global__ __launch_bounds__(C3_NT) void k_xi_sample(int nseg, const SegInfo *__
             // quadratic: what a step of 1e-9 leaves is below the rounding.  (Waiting
             // for steps of 1e-15 ran into the bracket's end at the root, which the
             // next step then left, and bisected the whole bracket again: 50
-            // evaluations of the score for 8.)
-            if (fabs(nx - al) <= 1e-9 * fmax(1.0, fabs(al))) {
+            // evaluations of the score for 8.)  A slope that overflows gives a step of 0.
+            if (fabs(nx - al) <= 1e-9 * fmax(1.0, fabs(al)) && isfinite(ds)) {
                 al = nx;
                 break;
             }
