@@ -323,8 +323,8 @@ __global__ __launch_bounds__(C3_NT) void k_resid(LayoutDev Ld, const int4 *__res
     const uint32_t npix = (uint32_t)Ld.band[band].npix;
     const int64_t npt = Ld.npix_total;
     const T *mp = maps + Ld.band[band].pix_off * (REC ? 4 : 1);
-    int cur = -1;
-    T mT = 0, mQ = 0, mU = 0;
+    int cur = -1;  // its map values are those of every pixel out of range
+    T mT = (T)NAN, mQ = (T)NAN, mU = (T)NAN;
     bool bad = false;
     for (int gi = 0; gi < tl.ngrp; ++gi) {
         const int seg = tl.first + gi;
