@@ -123,6 +123,7 @@ struct Plan {
         DevBuf tiles;
         int n = 0;
         int rev = 0;                      // revisits per tile part
+        double reads = 0;                 // pixel changes of all lanes, estimated
     };
     Tiles resid, chisq;                   // the residual's parts, the chi^2's
     int nbin = 0;
@@ -159,6 +160,7 @@ struct tod_ctx_s {
     DevBuf xi_bins, xi_part;
     std::map<uint64_t, std::unique_ptr<Plan>> plans;
     std::map<int, int> band_stride;       // band index -> stride (tuned or set)
+    std::map<int, double> band_repeat;    // band index -> part of the pixels that repeat at it (probed)
     std::map<std::string, int> stride_by_key;  // "nside:fsamp" -> stride (cache file)
     int64_t fft_batch = 0;                // complex elements per FFT batch (0: all segments)
     int bin_runs = 0;                     // scans per binning run (0: chosen per layout)
@@ -737,19 +739,20 @@ tod_status get_decode_tasks(tod_ctx ctx, Plan *P, int C, const DecodeTask **task
 
 // Revisit period of the pixel stream of a band: the lag with the most equal
 // pixels, probed on up to three of the band's segments.
+// repeat: the part of the samples compared whose pixel is the same one period later
 tod_status probe_stride(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t *pix, int band,
-                        int *stride) {
+                        int *stride, double *repeat) {
     const int maxlag = 16384;
     HIPCHK(ctx->probe_counts.ensure(sizeof(unsigned long long) * (maxlag + 1)));
     HIPCHK(c3::launch_zero(ctx->stream, ctx->probe_counts.p, sizeof(unsigned long long) * (maxlag + 1)));
-    int used = 0;
+    int used = 0, probed[3];
     for (int s = 0; s < L->nseg && used < 3; ++s) {
         if (L->h_seg_band[s] != band) continue;
         const SegInfo &g = P->h_segs[s];
         if (g.n < 2 * 64) continue;
         HIPCHK(c3::launch_repeat_probe(ctx->stream, pix, g.samp_off, g.n, std::min(maxlag, g.n - 1),
                                        (unsigned long long *)ctx->probe_counts.p));
-        ++used;
+        probed[used++] = g.n;
     }
     std::vector<unsigned long long> cnt(maxlag + 1);
     HIPCHK(hipMemcpyAsync(cnt.data(), ctx->probe_counts.p, cnt.size() * sizeof(unsigned long long),
@@ -763,6 +766,9 @@ tod_status probe_stride(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t
             best = l;
         }
     *stride = best > 0 ? best : 256;
+    int64_t compared = 0;
+    for (int i = 0; i < used; ++i) compared += std::max(0, std::min(probed[i] - best, C3_PROBE_MAX));
+    *repeat = best > 0 && compared > 0 ? std::min(1.0, (double)bc / (double)compared) : 0.0;
     return TOD_OK;
 }
 
@@ -786,9 +792,11 @@ tod_status get_bin_tiles(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_
         } else if ((int)P->bin_stride.size() == L->nband && P->bin_stride[b] > 0) {
             st[b] = P->bin_stride[b];  // the one this plan's tiles already use
         } else if (pix) {
-            tod_status r = probe_stride(ctx, L, P, pix, b, &st[b]);
+            double q;
+            tod_status r = probe_stride(ctx, L, P, pix, b, &st[b], &q);
             if (r != TOD_OK) return r;
             ctx->band_stride[b] = st[b];
+            ctx->band_repeat[b] = q;
         } else {
             st[b] = 256;
         }
@@ -820,6 +828,17 @@ tod_status get_bin_tiles(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_
             const std::vector<int4> v = xcd_order_tiles(split_tiles(tw, d == &P->resid ? kResidParts : kChisqParts, d->rev));
             HIPCHK(d->tiles.upload(v, ctx->stream));
             d->n = (int)v.size();
+            // a lane's pixel when its walk begins, and each time that it is not the last
+            // revisit's
+            d->reads = 0;
+            for (const int4 &t : v) d->reads += t.w & 0x1FF;
+            for (const TileWork &t : tw) {
+                const int band = P->h_segs[t.tile.x].band;
+                auto it = ctx->band_repeat.find(band);
+                // not probed: as the LFI scans have it
+                const double q = it != ctx->band_repeat.end() ? it->second : 0.9;
+                d->reads += (1.0 - q) * (t.tile.w & 0x1FF) * (t.visits - 1) * (t.tile.w >> 9 & 0x3F);
+            }
         }
         P->nbin = P->resid.n;
         P->bin_stride = st;
@@ -944,10 +963,25 @@ tod_status get_bin_runs(tod_ctx ctx, const tod_layout *L, Plan *P, const int32_t
 
 // The strided kernels read T, Q, U once per pixel change: three cache lines
 // from the [3][npix] maps, or one from records interleaved first, which costs
-// a pass over the whole map.  Interleaving all 12.6e6 pixels of nside 1024 takes
-// 55 us: with 1e8 samples over them the residual took 418 us with records and
-// 385 without; with 9.4e8 samples 3.00 ms with and 3.28 without.
-bool map_records(const tod_layout *L) { return L->nsamp >= 16 * L->npix_total; }
+// a pass over the whole map, twice as long in FP64, and a launch (55 us at nside 1024
+// in FP32, 14 at 512).  Residual, us, planes and records.  Segments shorter than the
+// period, by pixel changes a pixel of the map: nside 1024: 0.18 59 and 86, 0.39 109 and
+// 110, 0.56 166 and 130, 0.75 208 and 150; nside 512: 0.25 12 and 24, 1.0 53 and 40
+// (FP64: nside 1024 0.56 218 and 229, 0.75 278 and 252); the map adjoint gains more.  Long segments, where neighbouring lanes
+// share lines, by samples a pixel: nside 1024: 8 301 and 320, 15 570 and 555, 24 899 and
+// 827; nside 512: 29 281 and 271.
+bool map_records(const tod_layout *L, const Plan::Tiles &t, int mixed) {
+    if (L->nsamp >= 16 * L->npix_total) return true;
+    return t.reads >= 1e6 && t.reads >= (mixed ? 0.5 : 0.7) * (double)L->npix_total;
+}
+// the records' workspace where a launch of these tiles reads them, else NULL
+tod_status map_workspace(tod_ctx ctx, const tod_layout *L, const Plan::Tiles &t, int mixed, void **maps4) {
+    *maps4 = nullptr;
+    if (!map_records(L, t, mixed)) return TOD_OK;
+    HIPCHK(ctx->maps4.ensure((size_t)L->npix_total * 4 * (mixed ? 4 : 8)));
+    *maps4 = ctx->maps4.p;
+    return TOD_OK;
+}
 
 c3::BeginArgs begin_args(tod_ctx ctx, const double *sigma0, const double *fknee, const double *alpha, bool set_seed,
                          uint64_t seed, uint64_t iter) {
@@ -1278,11 +1312,11 @@ tod_status project_sky(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const 
     if ((r = get_plan(ctx, lay, mixed, &P)) != TOD_OK) return r;
     // strided tiles (the revisit period is probed from pix on first use)
     if ((r = get_bin_tiles(ctx, lay, P, pix)) != TOD_OK) return r;
-    const bool rec = map_records(lay);
-    if (rec) HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
+    void *maps4;
+    if ((r = map_workspace(ctx, lay, P->resid, mixed, &maps4)) != TOD_OK) return r;
     KTimer kt(ctx, K_PROJECT, ctx->stream);
     HIPCHK(c3::launch_resid_tiles(ctx->stream, make_layout_dev(lay), mixed, (const int4 *)P->resid.tiles.p, P->resid.n,
-                                  P->resid.rev, pix, psi, nullptr, 0, maps, rec ? ctx->maps4.p : nullptr, gain, mixed ? ctx->trig32.p : ctx->trig64.p, s_out,
+                                  P->resid.rev, pix, psi, nullptr, 0, maps, maps4, gain, mixed ? ctx->trig32.p : ctx->trig64.p, s_out,
                                   nullptr));
     return TOD_OK;
 }
@@ -1727,20 +1761,20 @@ static tod_status chisq_common(tod_ctx ctx, const tod_layout *lay, tod_prec prec
     for (double *g : {gsig, gfk, galpha})
         if (g) ba.zero(g, lay->ndet);
     // the map gradient gathers in records of four where the maps are read so
+    void *maps4;
+    if ((r = map_workspace(ctx, lay, P->chisq, mixed, &maps4)) != TOD_OK) return r;
     double *gm = grad_maps;
-    if (grad_maps && map_records(lay)) {
+    if (grad_maps && maps4) {
         HIPCHK(ctx->gmap4.ensure(sizeof(double) * 4 * (size_t)std::max<int64_t>(1, lay->npix_total)));
         gm = (double *)ctx->gmap4.p;
     }
     if (gm) HIPCHK(c3::launch_zero(st, gm, (int64_t)sizeof(double) * (gm == grad_maps ? 3 : 4) * lay->npix_total));
-    const bool rec = map_records(lay);
-    if (rec) HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
     const LayoutDev Ld = make_layout_dev(lay);
     HIPCHK(c3::launch_begin(st, Ld, ba, ctx->d_err));
     {
         KTimer kt(ctx, K_CHISQ, st);
         HIPCHK(c3::launch_chisq_time_tiles(st, Ld, mixed, (const int4 *)P->chisq.tiles.p, P->chisq.n, P->chisq.rev,
-                                           pix, psi, d, d_dtype == TOD_F64, ncorr, maps, rec ? ctx->maps4.p : nullptr, gain, sigma0, ctx->trig64.p,
+                                           pix, psi, d, d_dtype == TOD_F64, ncorr, maps, maps4, gain, sigma0, ctx->trig64.p,
                                            (double *)ctx->seg_sums.p, gm, gscale, gscale_dev));
         if (gm != grad_maps) HIPCHK(c3::launch_gmap_out(st, lay->npix_total, gm, grad_maps));
     }
@@ -1827,8 +1861,6 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
         if ((r = get_decode_tasks(ctx, P, tod->chunk_len, &dtt, &ndtt)) != TOD_OK) return r;
         HIPCHK(ctx->dec_tabs2.ensure(sizeof(DecTab) * (size_t)tod->ntable));
     }
-    const bool rec = map_records(lay);
-    if (rec) HIPCHK(ctx->maps4.ensure((size_t)lay->npix_total * 4 * (mixed ? 4 : 8)));
     hipStream_t st = ctx->stream;
     const LayoutDev Ld = make_layout_dev(lay);
     if (P->nbin > 0) {
@@ -1840,6 +1872,8 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
         int n0;
         if ((r = get_bin_runs(ctx, lay, P, nullptr, &t0, &n0, &r0)) != TOD_OK) return r;
     }
+    void *maps4;  // without tiles yet: chosen when the eager sequence has made them
+    if ((r = map_workspace(ctx, lay, P->resid, mixed, &maps4)) != TOD_OK) return r;
 
     // graph key: every pointer and size the captured kernels bake in -- the
     // layout and stream structs as the kernels receive them, the caller's
@@ -1856,7 +1890,7 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
     gk = fnv(gk, &Ht, sizeof(Ht));
     gk = fnv(gk, &quantum, sizeof(quantum));
     const void *ptrs[] = {d, maps, gain, sigma0, fknee, alpha, ncorr_out, acc, pix_work, psi_work,
-                          ctx->work.p, ctx->resid.p, ctx->dec_tabs.p, ctx->maps4.p, ctx->trig32.p,
+                          ctx->work.p, ctx->resid.p, ctx->dec_tabs.p, maps4, ctx->trig32.p,
                           ctx->trig64.p, ctx->d_err, ctx->d_seed_iter, dt, P->resid.tiles.p, P->run_tiles.p,
                           P->run_segs.p, ctx->dec_tabs2.p, dtt};
     gk = fnv(gk, ptrs, sizeof(ptrs));
@@ -1895,12 +1929,13 @@ static tod_status sweep_impl(tod_ctx ctx, const tod_layout *lay, tod_prec prec, 
         int nrt = P->nrun_tiles;
         if (!capture && !have_tiles) {
             tod_status rr = get_bin_runs(ctx, lay, P, pix_work, &rtiles, &nrt, &runs);
+            if (rr == TOD_OK) rr = map_workspace(ctx, lay, P->resid, mixed, &maps4);
             if (rr != TOD_OK) return rr;
         }
         {
             KTimer kt(ctx, K_PROJECT, st);
             HIPCHK(c3::launch_resid_tiles(st, Ld, mixed, (const int4 *)P->resid.tiles.p, P->resid.n,
-                                          P->resid.rev, pix_work, psi_work, d, d_dtype == TOD_F64, maps, rec ? ctx->maps4.p : nullptr, gain,
+                                          P->resid.rev, pix_work, psi_work, d, d_dtype == TOD_F64, maps, maps4, gain,
                                           mixed ? ctx->trig32.p : ctx->trig64.p, ctx->resid.p, ctx->d_err));
         }
         {
@@ -1979,6 +2014,7 @@ tod_status tod_set_bin_stride(tod_ctx ctx, int32_t band, int32_t stride) {
         ctx->band_stride.erase(band);
     else
         ctx->band_stride[band] = stride;
+    ctx->band_repeat.erase(band);
     return TOD_OK;
 }
 
@@ -2169,8 +2205,10 @@ tod_status tod_autotune(tod_ctx ctx, const tod_layout *lay, tod_prec prec, const
         if ((r = get_plan(ctx, lay, mixed, &P)) != TOD_OK) return r;
         for (int b = 0; b < lay->nband; ++b) {
             int st = 0;
-            if ((r = probe_stride(ctx, lay, P, pix, b, &st)) != TOD_OK) return r;
+            double q;
+            if ((r = probe_stride(ctx, lay, P, pix, b, &st, &q)) != TOD_OK) return r;
             ctx->band_stride[b] = st;
+            ctx->band_repeat[b] = q;
             ctx->stride_by_key[band_key(lay->bands[b])] = st;
         }
     }

@@ -169,6 +169,7 @@ struct alignas(16) DecTab {
 // y = first phase, z = stride S, w = lanes | group size << 9 | part << 15.
 // Part q covers the revisits [q rev, (q + 1) rev) of each segment.
 #define C3_TILE_MAXGRP 32
+#define C3_PROBE_MAX 8192    // samples of a segment that the repeat probe compares
 #define C3_TILE_MAXPART 65535
 inline int4 make_tile(int first, int phi0, int S, int nph, int ngrp, int part) {
     return make_int4(first, phi0, S, nph | (ngrp << 9) | (part << 15));

@@ -523,7 +523,7 @@ __global__ __launch_bounds__(C3_NT) void k_probe(const int32_t *__restrict__ pix
                                                  unsigned long long *counts) {
     const int L = blockIdx.x * C3_NT + threadIdx.x + 1;
     if (L > maxlag) return;
-    const int tmax = min(n - L, 8192);
+    const int tmax = min(n - L, C3_PROBE_MAX);
     unsigned long long c = 0;
     for (int t = 0; t < tmax; ++t) c += (pix[off + t] == pix[off + t + L]);
     atomicAdd(counts + L, c);
