@@ -73,14 +73,16 @@ def next5(n):
 # the sources each timed kernel family is compiled from (kernel code and the
 # headers it includes); its counter summary is valid while these are unchanged
 FAMILY_SOURCES = {
-    "decode": ["decode.hip", "common.h"],
+    "decode": ["decode.hip", "perdev.h", "common.h"],
     "project": ["pixel.hip", "common.h"],
     "bin": ["pixel.hip", "common.h"],
     "zero": ["pixel.hip", "common.h"],
-    "fft_col_fwd": ["fftcol.hip", "fftcol.h", "fftcold.hip", "fft.hip", "fftdev.h", "fftmode.h", "rng.h", "common.h"],
+    "fft_col_fwd": ["fftcol.hip", "fftcol.h", "fftcold.hip", "fft.hip", "fftdev.h", "fftmode.h", "rng.h", "tune.h", "perdev.h",
+                    "common.h"],
     "fft_row": ["fft.hip", "rowc.hip", "rowc.h", "rowc_body.h", "rowl.hip", "rowbody.h", "rowd.h", "rowd.hip", "rows.hip", "fp64fn.h",
-                "fftdev.h", "fftmode.h", "rng.h", "common.h"],
-    "fft_col_inv": ["fftcol.hip", "fftcol.h", "fftcold.hip", "fft.hip", "fftdev.h", "fftmode.h", "rng.h", "common.h"],
+                "fftdev.h", "fftmode.h", "rng.h", "tune.h", "perdev.h", "common.h"],
+    "fft_col_inv": ["fftcol.hip", "fftcol.h", "fftcold.hip", "fft.hip", "fftdev.h", "fftmode.h", "rng.h", "tune.h", "perdev.h",
+                    "common.h"],
 }
 
 

@@ -199,8 +199,9 @@ tod_status decode_flags(tod_ctx ctx, const tod_layout *lay, const tod_huff *flag
  * pix is out of range for the segment's band.  Samples are visited in strided
  * tiles of the band's revisit period: a band with no period set
  * (tod_set_bin_stride) or tuned (tod_autotune) has it probed from pix on the
- * first call, which waits for the stream.  Workspace: npix_total records of
- * four values, held by the context. */
+ * first call, which waits for the stream.  Workspace, where the samples change pixel
+ * often enough for the map's size: npix_total records of four values, held by
+ * the context. */
 tod_status project_sky(tod_ctx ctx, const tod_layout *lay, tod_prec prec,
                        const int32_t *pix, const uint16_t *psi,
                        const void *maps, const double *gain, void *s_out);
@@ -337,8 +338,7 @@ tod_status solve_maps(tod_ctx ctx, int64_t npix, const double *acc, double rcond
  * pixel is out of range for their band are left out of the time-domain sum.
  * The time-domain terms walk strided tiles of the band's revisit period
  * (probed from pix on the first call when not set or tuned, which waits for
- * the stream).  Workspace: npix_total records of four values, held by the
- * context. */
+ * the stream).  Workspace as project_sky's. */
 tod_status tod_chisq(tod_ctx ctx, const tod_layout *lay, tod_prec prec,
                      const int32_t *pix, const uint16_t *psi,
                      const void *d, tod_dtype d_dtype, const void *ncorr,
@@ -432,8 +432,10 @@ tod_status tod_set_bin_stride(tod_ctx ctx, int32_t band, int32_t stride);
  * and walks it through `scans` consecutive scans of one detector pair before
  * flushing its per-pixel sums, so the nearly coinciding rings of consecutive
  * scans share the flushes (section 2.4: binned on the fly, synchronised once).
- * Needs h_seg_det in the layout.  scans = 0: chosen per layout (as many as keep
- * about 4096 blocks), 1..16: fixed.  Correct for any value. */
+ * Needs h_seg_det in the layout.  scans = 0: chosen per layout, one scan for each
+ * 16384 tiles of 256 phases that runs of one scan would make (at least 1, at most
+ * 16; the tiles are cut along time afterwards), 1..16: fixed.  Correct for any
+ * value. */
 tod_status tod_set_bin_runs(tod_ctx ctx, int32_t scans);
 
 /* FFT work batching: the column/row passes run batch by batch over groups of

@@ -15,7 +15,8 @@
 // The decoders: k_decode32 and k_decode32_1 for chunks of 32 symbols (the
 // default spacing of the side index), k_decode and k_decode1 for longer
 // chunks, whose words would not fit a block's LDS, and for streams of 32-symbol
-// chunks too dense for it (over 23 bits a sample for the pointing).
+// chunks too dense for it (over 22 bits a sample for both streams of the pointing,
+// over 15 for one stream alone).
 //
 // k_decode: a block owns up to C3_DEC_NT consecutive chunks of one segment; each
 // thread parses one chunk of both streams from the side index, G codes per
@@ -414,8 +415,9 @@ __global__ __launch_bounds__(C3_DEC_NT) void k_decode(LayoutDev Ld, HuffDev hp, 
 // consecutive in the stream), the decoding tables and the symbol values as
 // 16-bit integers, most frequent first.  The window of the next 32 bits is one
 // two-word LDS read at the lane's bit position, so there is no look-ahead
-// state, and a lane writes its own 32 consecutive samples straight from
-// registers in 16-byte stores: no LDS tile, no barrier after the staging.
+// state.  A wave whose 64 chunks are whole swaps its samples between lanes and
+// stores contiguous lines (store_rows): no LDS tile, no barrier after the staging.
+// Short chunks, and blocks whose words do not fit, are stored sample by sample.
 // Symbols that do not fit (beyond the table's first KS entries, or wider than
 // 16 bits) are marked and read from memory, eight codes' together.
 //

@@ -32,10 +32,10 @@ struct FftChoice {
 
 // FP32: which of the row lengths that could share a launch get one of their own
 // (rowl.hip).  points[i]: row tasks times points a row, what length i costs.  In the
-// shared launch a length takes some 6 % longer; a launch more costs a tail, as much as
-// kOwnPoints save.  So a length of that many has its own launch, and the k others
-// either share one, or have k of their own where those k - 1 tails are saved; one that is
-// left alone always does.
+// shared launch a length takes some 6 % longer; a launch more costs a tail, what
+// kOwnPoints points lose there.  So a length of that many has its own launch, and the k
+// others share one unless together they lose more in it than the k - 1 tails it
+// saves; a length left alone never shares.
 constexpr int64_t kOwnPoints = 17000000;
 inline std::vector<char> own_rows(const std::vector<int64_t> &points) {
     std::vector<char> own(points.size(), 0);
