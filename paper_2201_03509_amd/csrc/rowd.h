@@ -4,7 +4,7 @@
 // Bound by FP64 and integer arithmetic (the mode draws, two Philox blocks a
 // pair).  On 9.2e6 samples of 1e5 to 1.3e5 a segment the draw's rows took 450 us on
 // the generic kernel, whose stages spilled and whose library functions were 700
-// of 1100 instructions a mode, and 176 here; the chi^2's (mode 1) 174 and 88.
+// of 1100 instructions a mode, and 178 here; the chi^2's (mode 1) 174 and 90.
 // Copying the rows in and out takes 60 us at 5.2 TB/s.
 #pragma once
 #include "rowbody.h"
